@@ -385,7 +385,7 @@ struct Builder {
   std::vector<TopkJob> tjobs;
   std::map<std::pair<int, int>, int> rowset_of;   // (head, row0) -> index
   int chunk_keys = 4096;
-  int max_tiles = 0, max_L = 0, max_chunks = 0, max_cands = 0, max_sel = 0;
+  int max_tiles = 0, max_L = 0, max_chunks = 0, max_cands = 0, max_sel = 0, max_topk_L = 0;
   int32_t* d_tpos = nullptr;
 
   int rowset(int head, int kvh, int row0, int nrows) {
@@ -447,6 +447,7 @@ struct Builder {
     n = std::min(n, L);
     int32_t* out = dalloc<int32_t>(P, std::max(n, 1));
     if (n > 0) tjobs.push_back({x, L, n, out});
+    max_topk_L = std::max(max_topk_L, L);
     max_sel = std::max(max_sel, n);
     return out;
   }
@@ -836,8 +837,8 @@ static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi
   HIPCHK(launch_est_udiag(d_jobs, (int)bd.jobs.size(), bd.max_L, st));
   mark(P, 1, st);
   HIPCHK(launch_grid_search(d_g, (int)bd.gjobs.size(), bd.max_cands, st));
-  int32_t* d_tscr = dalloc<int32_t>(P, topk_scratch_ints((int)bd.tjobs.size()));
-  HIPCHK(launch_topk(d_t, (int)bd.tjobs.size(), d_tscr, st));
+  int32_t* d_tscr = dalloc<int32_t>(P, topk_scratch_ints((int)bd.tjobs.size(), bd.max_topk_L));
+  HIPCHK(launch_topk(d_t, (int)bd.tjobs.size(), bd.max_topk_L, d_tscr, st));
   mark(P, 2, st);
 
   // permutations, key summaries, block counts
