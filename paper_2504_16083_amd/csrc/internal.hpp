@@ -165,6 +165,9 @@ int qb_order_chunks(int S);
 // k_estimate.hip
 // order: [ngrp][nr] member indices (-1 = none) of the groups that read the
 // same keys (row sets of one KV head; jobs of one KV head and key map).
+// est_chunk_keys: keys per chunk of the LSE pass for ngrp groups of nr row
+// sets over max_keys keys (a multiple of 64).
+int est_chunk_keys(int ngrp, int nr, int max_keys);
 hipError_t launch_est_lse(const RowSet* rs, int nrs, const int32_t* order, int ngrp, int nr, int max_chunks,
                           Tensor q, Tensor k, int chunk_keys, hipStream_t st);
 hipError_t launch_est_scores(const EstJob* jobs, int njobs, const int32_t* order, int ngrp, int nr, int max_tiles,

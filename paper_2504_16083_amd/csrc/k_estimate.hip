@@ -25,6 +25,8 @@
 // tile by all 64 rows; two tiles of rows in registers: tile t + 2 loads
 // while t and t + 1 are multiplied and reduced); the jobs of a group over
 // one range find it in that XCD's L2.
+#include <algorithm>
+
 #include "device.hpp"
 #include "internal.hpp"
 
@@ -196,32 +198,51 @@ __global__ __launch_bounds__(512) void k_est_lse(const RowSet* sets, const int32
   }
 }
 
-__global__ __launch_bounds__(64) void k_est_merge(const RowSet* sets) {
+// The chunks' (max, sum) pairs of every row folded in a fixed order: one lane
+// per row, wave w takes chunks w, w + MERGE_W, ... (running maximum, so each
+// partial is read once), then wave 0 folds the waves. One wave walking 256
+// chunks twice took 129 us at 1M tokens: the latency of one dependent step after
+// another.
+constexpr int MERGE_W = 16;
+
+__device__ __forceinline__ void fold_part(float& M, float& L, float m, float l) {
+  const float mn = fmaxf(M, m);
+  L = L * fast_exp2(M - mn) + l * fast_exp2(m - mn);
+  M = mn;
+}
+
+__global__ __launch_bounds__(64 * MERGE_W) void k_est_merge(const RowSet* sets) {
   const RowSet rs = sets[blockIdx.x];
-  const int r = threadIdx.x;
-  if (r >= rs.nrows) return;
-  float M = NEG_BIG;
-  for (int ch = 0; ch < rs.nchunks; ++ch) M = fmaxf(M, rs.part[((int64_t)ch * LASTQ + r) * 2]);
-  float L = 0.0f;
-  for (int ch = 0; ch < rs.nchunks; ++ch) {
-    const float* p = rs.part + ((int64_t)ch * LASTQ + r) * 2;
-    L += p[1] * fast_exp2(p[0] - M);
+  __shared__ float2 sh[MERGE_W][LASTQ];
+  const int r = threadIdx.x & 63, w = threadIdx.x >> 6;
+  float M = NEG_BIG, L = 0.0f;
+  if (r < rs.nrows) {
+    const float2* part = reinterpret_cast<const float2*>(rs.part);
+#pragma unroll 4
+    for (int ch = w; ch < rs.nchunks; ch += MERGE_W) {
+      const float2 p = part[(int64_t)ch * LASTQ + r];
+      fold_part(M, L, p.x, p.y);
+    }
   }
+  sh[w][r] = make_float2(M, L);
+  __syncthreads();
+  if (w > 0 || r >= rs.nrows) return;
+  for (int v = 1; v < MERGE_W; ++v) fold_part(M, L, sh[v][r].x, sh[v][r].y);
   rs.lse2[r] = M + fast_log2(L);
 }
 
 constexpr int APITCH = 65;   // floats per key row of A_hat in LDS: odd, so that the lanes of the
                              // diagonal sums (one diagonal each) read distinct banks
-constexpr int EST_TPW = 8;    // 64-key tiles per workgroup of the score pass
+constexpr int EST_TPW_MAX = 8;  // most 64-key tiles per workgroup of the score pass
 
-// Each workgroup takes EST_TPW consecutive tiles of one job: the query rows
+// Each workgroup takes tpw consecutive tiles of one job: the query rows
 // are loaded once, and the key positions and K rows of the tile after next
 // load while the current tile is reduced. The arithmetic of every tile is the same as
 // one tile per workgroup.
-// Logical item = (group, run of EST_TPW tiles, member): order[group * nr +
+// Logical item = (group, run of tpw tiles, member): order[group * nr +
 // member] is a job index (-1 = none), nrun runs per group.
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void k_est_scores(const EstJob* jobs, const int32_t* order, int ngrp, int nr,
-                                                    int nrun, const RowSet* sets, Tensor q, Tensor k) {
+                                                    int nrun, int tpw, const RowSet* sets, Tensor q, Tensor k) {
   __shared__ __align__(16) float ahat[B * APITCH];
   __shared__ int kposl[B];      // key positions of the current tile, INT_BIG past L_c
   const int64_t lg = run_item(blockIdx.x, nr);
@@ -231,9 +252,9 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void k
   const int ji = order[grp * nr + (int)(lg % nr)];
   if (ji < 0) return;
   const EstJob jb = jobs[ji];
-  const int ta = tr * EST_TPW;
+  const int ta = tr * tpw;
   if (ta >= jb.ntiles) return;
-  const int tb = min(ta + EST_TPW, jb.ntiles);
+  const int tb = min(ta + tpw, jb.ntiles);
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, c = lane & 31, h = lane >> 5;
   // wave w multiplies keys 32 w .. 32 w + 31 of each tile by all 64 rows
   // (each K row is loaded once per workgroup); lane (c, h) holds rows c and
@@ -340,22 +361,39 @@ static unsigned grouped_grid(int ngrp, int nper, int nr) {
   return (unsigned)((items + run - 1) / run * run);
 }
 
+// Keys per workgroup of the LSE pass: the pass is a serial chain of 64-key
+// tiles (about 1.6 us each) per workgroup, so short inputs are cut until
+// some EST_FILL workgroups run (four fit a CU); long ones keep 4096 keys, where a
+// chunk's partials and query loads cost nothing beside its tiles. 4096 keys
+// always: 105 us at 4K tokens and 2 heads, 83 us at 3K and 28 heads (a whole
+// layer 448 -> 338 and 536 -> 446 us with this and the score pass's rule).
+constexpr int EST_FILL = 1024, EST_CHUNK_MAX = 4096, EST_CHUNK_MIN = 128;
+
+int est_chunk_keys(int ngrp, int nr, int max_keys) {
+  const int64_t tiles = (int64_t)std::max(ngrp, 1) * ((std::max(nr, 1) + EMEM - 1) / EMEM) * ((max_keys + B - 1) / B);
+  const int64_t keys = (tiles + EST_FILL - 1) / EST_FILL * B;
+  return (int)std::min<int64_t>(EST_CHUNK_MAX, std::max<int64_t>(EST_CHUNK_MIN, keys));
+}
+
 hipError_t launch_est_lse(const RowSet* rs, int nrs, const int32_t* order, int ngrp, int nr, int max_chunks,
                           Tensor q, Tensor k, int chunk_keys, hipStream_t st) {
   if (nrs <= 0) return hipSuccess;
   const int nbat = (nr + EMEM - 1) / EMEM;
   hipLaunchKernelGGL(k_est_lse, dim3(grouped_grid(ngrp, max_chunks, nbat)), dim3(512), 0, st, rs, order, ngrp, nr,
                      nbat, max_chunks, q, k, chunk_keys);
-  hipLaunchKernelGGL(k_est_merge, dim3(nrs), dim3(64), 0, st, rs);
+  hipLaunchKernelGGL(k_est_merge, dim3(nrs), dim3(64 * MERGE_W), 0, st, rs);
   return hipGetLastError();
 }
 
 hipError_t launch_est_scores(const EstJob* jobs, int njobs, const int32_t* order, int ngrp, int nr, int max_tiles,
                              const RowSet* rs, Tensor q, Tensor k, hipStream_t st) {
   if (njobs <= 0) return hipSuccess;
-  const int nrun = (max_tiles + EST_TPW - 1) / EST_TPW;
+  // eight workgroups of two waves fit a CU: fewer tiles each until 2048 run
+  const int64_t tiles = (int64_t)njobs * max_tiles;
+  const int tpw = (int)std::min<int64_t>(EST_TPW_MAX, std::max<int64_t>(1, tiles / 2048));
+  const int nrun = (max_tiles + tpw - 1) / tpw;
   hipLaunchKernelGGL(k_est_scores, dim3(grouped_grid(ngrp, nrun, nr)), dim3(128), 0, st, jobs, order, ngrp, nr,
-                     nrun, rs, q, k);
+                     nrun, tpw, rs, q, k);
   return hipGetLastError();
 }
 

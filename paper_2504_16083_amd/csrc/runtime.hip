@@ -384,8 +384,7 @@ struct Builder {
   std::vector<GridJob> gjobs;
   std::vector<TopkJob> tjobs;
   std::map<std::pair<int, int>, int> rowset_of;   // (head, row0) -> index
-  int chunk_keys = 4096;
-  int max_tiles = 0, max_L = 0, max_chunks = 0, max_cands = 0, max_sel = 0, max_topk_L = 0;
+  int max_tiles = 0, max_L = 0, max_keys = 0, max_cands = 0, max_sel = 0, max_topk_L = 0;
   int32_t* d_tpos = nullptr;
 
   int rowset(int head, int kvh, int row0, int nrows) {
@@ -394,10 +393,8 @@ struct Builder {
     if (it != rowset_of.end()) return it->second;
     RowSet r{};
     r.head = head; r.kvh = kvh; r.row0 = row0; r.nrows = nrows;
-    r.nchunks = (row0 + nrows + chunk_keys - 1) / chunk_keys;
-    r.part = dalloc<float>(P, (size_t)r.nchunks * LASTQ * 2);
     r.lse2 = dalloc<float>(P, LASTQ);
-    max_chunks = std::max(max_chunks, r.nchunks);
+    max_keys = std::max(max_keys, row0 + nrows);
     rowsets.push_back(r);
     P->est_lse2.push_back(r.lse2);
     P->rowset_n.push_back(nrows);
@@ -810,6 +807,12 @@ static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi
     return std::make_pair((int64_t)bd.rowsets[i].kvh, (int64_t)0); }, rs_ngrp, rs_nr);
   const std::vector<int32_t> job_order = grouped((int)bd.jobs.size(), [&](int i) {
     return std::make_pair((int64_t)bd.jobs[i].kvh, (int64_t)(intptr_t)bd.jobs[i].keymap); }, job_ngrp, job_nr);
+  const int chunk_keys = est_chunk_keys(rs_ngrp, rs_nr, bd.max_keys);
+  const int max_chunks = (bd.max_keys + chunk_keys - 1) / chunk_keys;
+  for (RowSet& r : bd.rowsets) {
+    r.nchunks = (r.row0 + r.nrows + chunk_keys - 1) / chunk_keys;
+    r.part = dalloc<float>(P, (size_t)r.nchunks * LASTQ * 2);
+  }
   int32_t *d_rs_order = nullptr, *d_job_order = nullptr;
   RowSet* d_rs = nullptr;
   EstJob* d_jobs = nullptr;
@@ -830,8 +833,8 @@ static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi
     send(P, pk);
   }
   mark(P, 0, st);
-  HIPCHK(launch_est_lse(d_rs, (int)bd.rowsets.size(), d_rs_order, rs_ngrp, rs_nr, bd.max_chunks, tq, tk,
-                        bd.chunk_keys, st));
+  HIPCHK(launch_est_lse(d_rs, (int)bd.rowsets.size(), d_rs_order, rs_ngrp, rs_nr, max_chunks, tq, tk,
+                        chunk_keys, st));
   HIPCHK(launch_est_scores(d_jobs, (int)bd.jobs.size(), d_job_order, job_ngrp, job_nr, bd.max_tiles, d_rs, tq,
                            tk, st));
   HIPCHK(launch_est_udiag(d_jobs, (int)bd.jobs.size(), bd.max_L, st));
