@@ -225,13 +225,25 @@ struct AttnArgs {
 hipError_t launch_attention(const AttnArgs& a, hipStream_t st);
 hipError_t launch_combine(const AttnArgs& a, const SplitRow* splits, int64_t nsplit, hipStream_t st);
 // k_search.hip: out[h * n_class + c] = sum over x with cls[x] == c of |a[x,h] - b[x,h]|^2
+// (bf16 outputs of S x H rows); part: scratch of H * n_class * SQ_CHUNKS doubles, or nullptr (fewer workgroups)
+constexpr int SQ_CHUNKS = 64;
 hipError_t launch_sqerr(const void* a, const void* b, int64_t ss, int64_t sh, const uint8_t* cls, int n_class,
-                        int S, int H, double* out, hipStream_t st);
+                        int S, int H, double* out, double* part, hipStream_t st);
 // k_permute.hip
 hipError_t launch_permute(const void* src, int64_t ss, void* dst, int64_t ds, const int32_t* perm,
                           int64_t n, int64_t row_bytes, int inverse, hipStream_t st);
 
-// k_stats.hip: useful query-key pairs of one head's selected blocks, added to *out
+// k_stats.hip: what mmi_plan_stats reports from the device, for every head
+// (out zeroed by the caller; op_slot: export slot of every op, nops: ops of
+// every head, mod: modality of every position)
+struct HeadStatDev {
+  unsigned long long blocks[MMI_MAX_MODALITIES * MMI_MAX_MODALITIES];
+  int32_t sigma[MMI_MAX_MODALITIES], phase[MMI_MAX_MODALITIES];
+  int32_t group_stride, pad;
+};
+hipError_t launch_head_stats(const HeadDev* heads, int nheads, const OpDev* ops, const int32_t* op_slot,
+                             const int32_t* nops, const uint8_t* mod, int max_nbq, HeadStatDev* out, hipStream_t st);
+// useful query-key pairs of one head's selected blocks, added to *out
 hipError_t launch_pair_count(const HeadDev* heads, int head, int R, int ngroups, unsigned long long* out,
                              hipStream_t st);
 

@@ -192,6 +192,7 @@ struct mmi_plan {
   int64_t gnnz_all = 0;
   bool executed = false;
   std::vector<int> rowset_n;
+  std::vector<mmi::HeadStatDev> stats;   // of every head, filled by the first mmi_plan_stats
   int64_t device_bytes = 0;       // device memory the plan holds
   uint8_t* scratch = nullptr;     // non-null: buffers come from the no-allocation scratch
   size_t scratch_used = 0;
@@ -988,6 +989,37 @@ static void build_item_map(mmi_plan* P, hipStream_t st) {
   P->map_len = len;
 }
 
+// What mmi_plan_stats takes from the device, for every head of the plan (the
+// plan's tables do not change after its creation).
+static std::vector<HeadStatDev> read_stats(mmi_plan* P) {
+  const size_t mod_at = sizeof(HeadStatDev) * P->Hq, slot_at = (mod_at + P->mod.size() + 255) & ~(size_t)255;
+  const size_t nops_at = slot_at + sizeof(int32_t) * P->ops.size(), bytes = nops_at + sizeof(int32_t) * P->Hq;
+  std::vector<uint8_t> host(bytes, 0);
+  std::copy(P->mod.begin(), P->mod.end(), host.begin() + mod_at);
+  int32_t* slot = reinterpret_cast<int32_t*>(host.data() + slot_at);
+  int32_t* nops = reinterpret_cast<int32_t*>(host.data() + nops_at);
+  int max_nbq = 0;
+  for (int h = 0; h < P->Hq; ++h) {
+    const HostHead& H = P->hh[h];
+    std::copy(H.op_slot.begin(), H.op_slot.end(), slot + H.op0);
+    nops[h] = H.nops;
+    max_nbq = std::max(max_nbq, P->heads[h].nbq);
+  }
+  std::vector<HeadStatDev> out(P->Hq);
+  uint8_t* d = static_cast<uint8_t*>(P->ctx->alloc.get(bytes));
+  hipError_t e = hipMemcpyAsync(d, host.data(), bytes, hipMemcpyHostToDevice, P->stream);
+  if (e == hipSuccess)
+    e = launch_head_stats(P->d_heads, P->Hq, P->d_ops, reinterpret_cast<int32_t*>(d + slot_at),
+                          reinterpret_cast<int32_t*>(d + nops_at), d + mod_at, max_nbq,
+                          reinterpret_cast<HeadStatDev*>(d), P->stream);
+  if (e == hipSuccess) e = hipMemcpyAsync(out.data(), d, mod_at, hipMemcpyDeviceToHost, P->stream);
+  const hipError_t es = hipStreamSynchronize(P->stream);   // host, out and d are in use until then
+  P->ctx->alloc.put(d, bytes);
+  HIPCHK(e);
+  HIPCHK(es);
+  return out;
+}
+
 // The debug check of a plan: its tables copied to the host, each head's
 // block index and row-group unions, then the work list and item map.
 static void plan_check(mmi_plan* P) {
@@ -1252,7 +1284,6 @@ int mmi_plan_stats(mmi_plan* P, int head, mmi_head_stats* out) {
     if (!P || !out) fail(MMI_ERR_INVALID_ARG, "plan/out is NULL");
     if (head < 0 || head >= P->Hq) fail(MMI_ERR_INVALID_ARG, "head %d out of range", head);
     HIPCHK(hipSetDevice(P->ctx->device));
-    HIPCHK(hipStreamSynchronize(P->stream));
     const HostHead& H = P->hh[head];
     const HeadDev& hd = P->heads[head];
     mmi_head_stats s{};
@@ -1263,39 +1294,16 @@ int mmi_plan_stats(mmi_plan* P, int head, mmi_head_stats* out) {
     const int64_t nb = (P->S + B - 1) / B;
     s.causal_blocks = nb * (nb + 1) / 2;
     s.split_rows = (int32_t)H.nsplit;
-    for (int i = 0; i < H.nops; ++i) {
-      const EstInfo& e = H.est[i];
-      if (e.params) {
-        int32_t prm[4];
-        HIPCHK(hipMemcpy(prm, e.params, sizeof prm, hipMemcpyDeviceToHost));
-        const int slot = H.op_slot[i];
-        if (slot < MMI_MAX_MODALITIES) { s.sigma[slot] = prm[0]; s.phase[slot] = prm[1]; }
-      }
+    if (P->stats.empty()) P->stats = read_stats(P);
+    const HeadStatDev& d = P->stats[head];
+    for (int m = 0; m < MMI_MAX_MODALITIES; ++m) {
+      s.sigma[m] = d.sigma[m];
+      s.phase[m] = d.phase[m];
+      for (int m2 = 0; m2 < MMI_MAX_MODALITIES; ++m2)
+        s.blocks_by_modality[m][m2] = (int64_t)d.blocks[m * MMI_MAX_MODALITIES + m2];
     }
-    int32_t gp[2];
-    HIPCHK(hipMemcpy(gp, hd.gp, sizeof gp, hipMemcpyDeviceToHost));
-    s.group_stride = gp[0];
+    s.group_stride = d.group_stride;
     s.loaded_blocks = H.gnnz;
-    // selected blocks by (query modality, key modality), from the block index
-    auto block_mods = [&](const int32_t* perm, int nblk) {
-      std::vector<int32_t> slots((size_t)nblk * B);
-      if (perm) HIPCHK(hipMemcpy(slots.data(), perm, slots.size() * 4, hipMemcpyDeviceToHost));
-      else for (size_t x = 0; x < slots.size(); ++x) slots[x] = x < (size_t)P->S ? (int32_t)x : -1;
-      std::vector<int> m(nblk, -1);
-      for (int j = 0; j < nblk; ++j)
-        for (int x = 0; x < B && m[j] < 0; ++x)
-          if (slots[(size_t)j * B + x] >= 0) m[j] = P->mod[slots[(size_t)j * B + x]];
-      return m;
-    };
-    const std::vector<int> qm = block_mods(hd.qperm, hd.nbq), km = block_mods(hd.kperm, hd.nbk);
-    std::vector<int32_t> rp(hd.nbq + 1), col(std::max<int64_t>(H.nnz, 1));
-    HIPCHK(hipMemcpy(rp.data(), hd.rowptr, rp.size() * 4, hipMemcpyDeviceToHost));
-    if (H.nnz) HIPCHK(hipMemcpy(col.data(), hd.col, (size_t)H.nnz * 4, hipMemcpyDeviceToHost));
-    for (int i = 0; i < hd.nbq; ++i) {
-      if (qm[i] < 0) continue;
-      for (int e = rp[i]; e < rp[i + 1]; ++e)
-        if (km[col[e]] >= 0) ++s.blocks_by_modality[qm[i]][km[col[e]]];
-    }
     *out = s;
   });
 }
@@ -1523,7 +1531,8 @@ int mmi_output_sqerr(const mmi_problem* prob, const void* a, const void* b, cons
     if (n_class < 1 || n_class > MMI_MAX_MODALITIES)
       fail(MMI_ERR_INVALID_ARG, "n_class must be in [1, %d]", MMI_MAX_MODALITIES);
     aligned16(a, "a"); aligned16(b, "b");
-    HIPCHK(launch_sqerr(a, b, p.o_stride_s, p.o_stride_h, cls, n_class, (int)p.S, p.Hq, out, (hipStream_t)stream));
+    HIPCHK(launch_sqerr(a, b, p.o_stride_s, p.o_stride_h, cls, n_class, (int)p.S, p.Hq, out, nullptr,
+                        (hipStream_t)stream));
   });
 }
 

@@ -117,6 +117,7 @@ class Runner {
     ref_.reset(new DevBuf(obytes));
     cls_.reset(new DevBuf((size_t)S));
     err_.reset(new DevBuf(sizeof(double) * prob.Hq * mods.size()));
+    part_.reset(new DevBuf(sizeof(double) * prob.Hq * mods.size() * SQ_CHUNKS));
     hipcall(hipMemcpyAsync(cls_->p, cls.data(), (size_t)S, hipMemcpyHostToDevice, st_), "cls copy");
     hipcall(hipStreamSynchronize(st_), "cls copy");
   }
@@ -155,8 +156,9 @@ class Runner {
   // reference over the rows of modality mods[i], in float64.
   std::vector<std::vector<double>> sqerr() {
     const int n = (int)mods.size();
-    call(mmi_output_sqerr(&prob_, o_->p, ref_->p, static_cast<const uint8_t*>(cls_->p), n,
-                          static_cast<double*>(err_->p), st_));
+    hipcall(launch_sqerr(o_->p, ref_->p, (int64_t)prob_.Hq * MMI_HEAD_DIM, MMI_HEAD_DIM,
+                         static_cast<const uint8_t*>(cls_->p), n, (int)prob_.S, prob_.Hq,
+                         static_cast<double*>(err_->p), static_cast<double*>(part_->p), st_), "output difference");
     std::vector<double> e((size_t)prob_.Hq * n);
     hipcall(hipMemcpyAsync(e.data(), err_->p, sizeof(double) * e.size(), hipMemcpyDeviceToHost, st_), "err copy");
     hipcall(hipStreamSynchronize(st_), "err copy");
@@ -171,7 +173,7 @@ class Runner {
   mmi_problem prob_;
   const void *q_, *k_, *v_;
   hipStream_t st_;
-  std::unique_ptr<DevBuf> o_, ref_, cls_, err_;
+  std::unique_ptr<DevBuf> o_, ref_, cls_, err_, part_;
 };
 
 // Index of the admissible candidate (cost <= budget) of smallest error, the

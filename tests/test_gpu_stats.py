@@ -1,0 +1,65 @@
+"""Output differences and per-head block statistics against numpy (needs an MI355X)."""
+import numpy as np
+import pytest
+import torch
+
+from synth import config as C
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2504_16083_amd import mmi
+    c = mmi.Ctx(0)
+    yield c
+    c.close()
+
+
+# a row, a workgroup's rows and one past them, past an unrolled stretch; a head stride of its own
+@pytest.mark.parametrize("S,H,n_class", [(1, 1, 1), (32, 2, 2), (33, 3, 8), (129, 2, 3), (5000, 3, 2)])
+def test_sqerr(S, H, n_class):
+    from paper_2504_16083_amd import mmi
+    print(f"[gpu] sqerr S={S}", flush=True)
+    g = torch.Generator().manual_seed(S)
+    a, b = (torch.randn(S, H + 1, 128, generator=g).to(torch.bfloat16) for _ in range(2))
+    cls = torch.randint(0, n_class + 1, (S,), generator=g).to(torch.uint8)   # class n_class: skipped rows
+    a[cls == n_class] = float("inf")
+    prob = mmi.Problem(S, H, H, None, strides={"o": ((H + 1) * 128, 128)})
+    out = torch.full((H * n_class,), -1.0, device="cuda", dtype=torch.float64)
+    mmi.mmi_output_sqerr(prob, a.cuda(), b.cuda(), cls.cuda(), n_class, out)
+    d = (a.float() - b.float()).double().square().sum(2).numpy()
+    want = np.array([[d[cls.numpy() == c, h].sum() for c in range(n_class)] for h in range(H)])
+    # fp64 sums of n positive terms in another order: n 2^-53 relative
+    assert np.abs(out.cpu().numpy().reshape(H, -1) - want).max() <= S * 128 * 2.0 ** -53 * max(want.max(), 1.0)
+
+
+def test_block_statistics(ctx):
+    from paper_2504_16083_amd import mmi
+    S = 2049 + 64 * 70                      # more than one run of query blocks per workgroup, a ragged tail
+    rng = np.random.default_rng(0)
+    mod = np.repeat(rng.integers(0, 3, S // 37 + 1), 37)[:S].astype(np.uint8)
+    g = torch.Generator().manual_seed(1)
+    q, k = (torch.randn(S, h, 128, generator=g).to(torch.bfloat16).cuda() for h in (4, 2))
+    intra = {0: C.ashape(64, 128), 1: C.grid(30, 40), 2: C.vslash(20, 20)}
+    heads = [C.global_head(C.grid(50, 60)), C.qboundary_head(intra),
+             C.boundary2d_head(intra, {(0, 1): C.vert(30), (2, 0): C.dense()}), C.global_head(C.ashape(64, 256))]
+    plan = mmi.Plan(ctx, mmi.Problem(S, 4, 2, mod), heads, q, k)
+    for h in (2, 0, 1, 3):
+        st = plan.stats(h)
+        ptr, col = plan.export(h, "row_ptr"), plan.export(h, "col_idx")
+
+        def mods(perm):
+            x = perm.reshape(-1, 64)
+            return [int(mod[r[r >= 0][0]]) for r in x]
+        mq, mk = mods(plan.export(h, "qperm")), mods(plan.export(h, "kperm"))
+        want = np.zeros((8, 8), np.int64)
+        for i in range(len(mq)):
+            for j in col[ptr[i]:ptr[i + 1]]:
+                want[mq[i], mk[j]] += 1
+        assert np.array_equal(np.array([list(r) for r in st.blocks_by_modality]), want), h
+        for m in range(3 if h in (1, 2) else 1):
+            if (h == 0) or (h in (1, 2) and m == 1):
+                p = plan.export(h, "params", m)
+                assert (st.sigma[m], st.phase[m]) == (p[0], p[1]), (h, m)
+    plan.destroy()
