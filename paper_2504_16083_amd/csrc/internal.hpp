@@ -114,11 +114,9 @@ struct HeadDev {
   // (g / rho) * R * rho + g % rho + r * rho; rho is chosen per head.
   int32_t gcap;               // capacity of the per-group arrays (>= groups for any stride)
   int32_t rho_alt[2];         // extra row-stride candidates besides 1, 2, 4, 8 (0 = none)
-  int32_t* gp;                // [3] chosen row stride rho, number of groups, index of rho among the candidates
-  int32_t* gcount;            // [groups] union sizes
+  int32_t* gp;                // [2] chosen row stride rho, number of groups
   int32_t* growptr;           // [ngroups+1]
   int32_t* gcol;              // [gnnz] union entries: key block, select flags << 16, mask flags << 24
-  int32_t* chunklen;          // [1] union entries per work item for this head (set by the scan)
   int32_t* chunks;            // [ngroups] work items per group
   int32_t* itembase;          // [ngroups] exclusive prefix of chunks
   int32_t* splitoff;          // [ngroups] exclusive prefix of (chunks > 1)
@@ -144,7 +142,8 @@ struct QbOrderJob {   // phase order of one Q-Boundary Grid modality's queries
 struct WorkItem {
   int32_t head, group, e0, e1;   // union entries [e0, e1) of row group `group`
   int32_t part;       // -1: write O directly; else partial slot
-  int32_t pad[3];
+  int32_t lead;       // > 0: start beside the items of the run; at most this many steps' worth of waiting
+  int32_t pad[2];
 };
 
 struct SplitRow {     // a row group whose union list is split over several items
@@ -182,31 +181,43 @@ hipError_t launch_topk(const TopkJob* jobs, int njobs, int max_L, int32_t* scr, 
 // k_blocks.hip
 hipError_t launch_key_summaries(const HeadDev* heads, int nheads, OpDev* ops, int nops,
                                 Groups g, int max_nbk, int max_sel, hipStream_t st);
-hipError_t launch_blocks_count(const HeadDev* heads, int nheads, const OpDev* ops, Groups g, int max_nbq,
-                               hipStream_t st);
-// Chooses each head's row stride rho among 1, 2, 4, 8 and the head's
-// rho_alt (smallest total union, ties to the earlier candidate); cand: int64
-// scratch [nheads][NRHO]; extra: some head has rho_alt candidates.
+// cand: int64 [nheads][NRHO], cleared by this launch for launch_group_stride
 constexpr int NRHO = 6;
+hipError_t launch_blocks_count(const HeadDev* heads, int nheads, const OpDev* ops, Groups g, int max_nbq,
+                               int64_t* cand, hipStream_t st);
+// Union sizes of every row group for each head's candidate row strides 1, 2,
+// 4, 8 and its rho_alt (gcnt [nheads][NRHO][max_groups]) and their totals
+// (cand); extra: some head has rho_alt candidates.
 hipError_t launch_group_stride(const HeadDev* heads, int nheads, int R, int max_groups, int max_nbq, bool extra,
                                int64_t* cand, int32_t* gcnt, hipStream_t st);
-hipError_t launch_group_count(const HeadDev* heads, int nheads, const int32_t* gcnt, int max_groups,
-                              hipStream_t st);
-// totals[head] = {nnz, gnnz, nitems, nsplit, nparts}
+// Each head's stride (smallest total union, ties to the earlier candidate)
+// and offsets; totals[head] = {nnz, gnnz, nitems, nsplit, nparts}. A union is
+// split into work items beyond max(min_chunk, staged blocks of the layer /
+// items) entries; min_chunk 0: from the average union of the all_groups groups.
 constexpr int NTOT = 5;
-// Work-item length per head: max(min_chunk, ceil(gnnz_head / items_per_head),
-// avg_factor x the head's average group union) (avg_factor 0: no such floor).
-hipError_t launch_blocks_scan(const HeadDev* heads, int nheads, int min_chunk, int items_per_head, int avg_factor,
-                              int64_t* totals, hipStream_t st);
+hipError_t launch_blocks_scan(const HeadDev* heads, int nheads, int R, const int64_t* cand, const int32_t* gcnt,
+                              int max_groups, int min_chunk, int items, int all_groups, int64_t* totals, hipStream_t st);
 hipError_t launch_blocks_fill(const HeadDev* heads, int nheads, int max_nbq, int R, int max_groups,
                               hipStream_t st);
-// Modelled cost of each work item (its union entries: one staged K/V block
-// each, plus one computed block per member that selects it).
-hipError_t launch_item_cost(const HeadDev* heads, const WorkItem* items, int64_t nitems, float* cost,
-                            hipStream_t st);
-hipError_t launch_work_fill(const HeadDev* heads, int nheads, const int64_t* item_base,
+// Runs of consecutive work items and their slots in the item map ([8][cap *
+// run], -1 = none): 32 items per run, fewer for small layers so that every XCD
+// gets some, more where there would be over MAP_RUNS runs; at most a quarter
+// more runs on an XCD than the average.
+constexpr int MAP_RUNS = 4096, MAP_CAP = MAP_RUNS / 8 + MAP_RUNS / 32 + 2;
+struct MapShape {
+  int32_t run, nruns, cap;
+};
+inline MapShape map_shape(int64_t n) {
+  int64_t run = n / 64 < 1 ? 1 : n / 64 < 32 ? n / 64 : 32;
+  if (n > run * MAP_RUNS) run = (n + MAP_RUNS - 1) / MAP_RUNS;
+  const int64_t nruns = (n + run - 1) / run, avg = (nruns + 7) / 8;
+  return {(int32_t)run, (int32_t)nruns, (int32_t)(avg + (avg / 4 > 1 ? avg / 4 : 1))};
+}
+hipError_t launch_work_fill(const HeadDev* heads, int nheads, int R, const int64_t* item_base,
                             const int64_t* part_base, const int64_t* split_base, int max_groups,
-                            WorkItem* items, SplitRow* splits, hipStream_t st);
+                            WorkItem* items, float* cost, SplitRow* splits, hipStream_t st);
+// also clears queues[nqueues]
+hipError_t launch_item_map(const float* cost, int64_t n, int32_t* map, int32_t* queues, int nqueues, hipStream_t st);
 // k_attention.hip
 struct AttnArgs {
   Tensor q, k, v;
@@ -218,10 +229,16 @@ struct AttnArgs {
   int64_t nitems;
   const int32_t* item_map;    // [8][map_len]: work items of each XCD in order, -1 = none
   int64_t map_len;
+  int32_t map_run;            // consecutive entries of a list that are neighbouring items
   float* part_o;              // [nparts][R*64][128], each row normalised by its bf16-P sum
   float* part_ml;             // [nparts][R*64][4]: running max m, bf16-P sum lo, fp32-P sum l, unused
   int32_t R;                  // query blocks per row group (1, 2 or 4)
+  int32_t* queue;             // QUEUE_INTS zeroed counters of one launch at a time (left zeroed), or
+                              // nullptr: one workgroup per item
+  int32_t cus;                // persistent workgroups (a multiple of 8)
 };
+constexpr int QUEUE_LINE = 32;              // one counter per 128 bytes
+constexpr int QUEUE_INTS = 17 * QUEUE_LINE; // entries taken of 8 lists, entries finished, workgroups through
 hipError_t launch_attention(const AttnArgs& a, hipStream_t st);
 hipError_t launch_combine(const AttnArgs& a, const SplitRow* splits, int64_t nsplit, hipStream_t st);
 // k_search.hip: out[h * n_class + c] = sum over x with cls[x] == c of |a[x,h] - b[x,h]|^2

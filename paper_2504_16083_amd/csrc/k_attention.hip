@@ -49,6 +49,8 @@ constexpr int KPITCH = 136;   // bf16 per K row in LDS (272 B): conflict-free 16
 constexpr int VPITCH = 160;   // bf16 per V row in LDS (320 B): transpose reads of 4 rows hit distinct banks
 constexpr int NSTAGE = 4;
 constexpr float RESCALE_SLACK = 8.0f;
+constexpr int LEAD_SLACK = 2;            // items of the run before that may still be running
+constexpr int LEAD_TICKS = 30;           // longest wait per union entry of the item, 10 ns ticks
 
 struct __align__(16) Stage {
   uint16_t k[B * KPITCH];
@@ -60,6 +62,32 @@ struct __align__(16) Stage {
 // would become a flat load, which also counts against the LDS wait counter).
 __device__ __forceinline__ int ld_global(const int32_t* p) {
   return *(const __attribute__((address_space(1))) int32_t*)(p);
+}
+
+// Plan tables are read through the constant address space (this launch does
+// not write them), so that what they hold stays in scalar registers also
+// after the first item's stores.
+#define CONST_AS __attribute__((address_space(4)))
+
+__device__ __forceinline__ WorkItem load_item(const AttnArgs& a, int it) {
+  const CONST_AS WorkItem* p = (const CONST_AS WorkItem*)(a.items + it);
+  WorkItem w;
+  w.head = p->head; w.group = p->group; w.e0 = p->e0; w.e1 = p->e1; w.part = p->part; w.lead = p->lead;
+  return w;
+}
+
+struct ItemHead {              // what the kernel needs of a HeadDev
+  int32_t kvh, causal, nbq, rho;
+  const int32_t *qperm, *kperm, *gcol;
+};
+
+__device__ __forceinline__ ItemHead load_head(const AttnArgs& a, int head) {
+  const CONST_AS HeadDev* p = (const CONST_AS HeadDev*)(a.heads + head);
+  ItemHead h;
+  h.kvh = p->kvh; h.causal = p->causal; h.nbq = p->nbq;
+  h.qperm = p->qperm; h.kperm = p->kperm; h.gcol = p->gcol;
+  h.rho = *(const CONST_AS int32_t*)(p->gp);
+  return h;
 }
 
 __device__ __forceinline__ int slot_pos(const int32_t* perm, int slot, int S) {
@@ -92,7 +120,7 @@ struct KeySrc {
   uint32_t cb;                // this thread's chunk offset in bytes
   const int32_t* perm;
   int S, key0;
-  __device__ __forceinline__ void init(const AttnArgs& a, const HeadDev& hd, int tid) {
+  __device__ __forceinline__ void init(const AttnArgs& a, const ItemHead& hd, int tid) {
     const uint16_t* kb = reinterpret_cast<const uint16_t*>(a.k.p) + (int64_t)hd.kvh * a.k.sh;
     const uint16_t* vb = reinterpret_cast<const uint16_t*>(a.v.p) + (int64_t)hd.kvh * a.v.sh;
     kss = (uint32_t)a.k.ss * 2u;
@@ -172,11 +200,12 @@ struct EntryStream {
 };
 
 // Work-item order: hardware hands consecutive workgroups to the 8 XCDs in
-// turn, so workgroup b runs on XCD b mod 8 as that XCD's (b / 8)-th. The
+// turn, so workgroup b runs on XCD b mod 8 (without a queue, as that XCD's
+// (b / 8)-th). The
 // plan's item map lists each XCD's items in order (runs of neighbouring row
 // groups, which share key blocks in that XCD's L2, balanced over the XCDs by
 // modelled cost).
-__device__ __forceinline__ int64_t item_of_block(const AttnArgs& a, int64_t b) {
+__device__ __forceinline__ int item_of_block(const AttnArgs& a, int b) {
   const int64_t k = b >> 3;
   return k < a.map_len ? a.item_map[(b & 7) * a.map_len + k] : -1;
 }
@@ -444,34 +473,40 @@ __device__ __forceinline__ void block_step(WaveState& ws, Stage* stg, const KeyS
   __syncthreads();
 }
 
-template <int R, bool PERM, bool CAUSAL, bool WL>
-__device__ __forceinline__ void block_loop(WaveState& ws, Stage* stg, const AttnArgs& a, const HeadDev& hd,
-                                           const WorkItem& w, int tid) {
+// The block loop of one work item; load_q fills the wave's query rows (called
+// once, behind the first key rows in the load queue).
+template <int R, bool PERM, bool CAUSAL, bool WL, typename F>
+__device__ __forceinline__ void block_loop(WaveState& ws, Stage* stg, const AttnArgs& a, const ItemHead& hd,
+                                           const WorkItem& w, EntryStream& es, int tid, F load_q) {
   KeySrc<R> ks;
   ks.init(a, hd, tid);
   const float sc = 0.08838834764831845f * LOG2E;   // sqrt(1/128) * log2(e)
   const int n = w.e1 - w.e0;
-  EntryStream es;
-  es.init(hd.gcol + w.e0, n, tid & 63);
   int e0 = es.get(0), e1 = es.get(1), e2 = es.get(2), e3 = es.get(3), e4 = es.get(4);
 
-  // prologue: blocks 0-2 staged, block 3 loading, positions of block 4
+  // prologue: blocks 0-2 staged, block 3 loading, positions of block 4. All
+  // positions are asked for first, then all rows, so that an item waits for
+  // two load latencies and not for two per block. Blocks past the end read
+  // key block 0 (entry 0) and are not staged.
   BlockRegs<R> regs;
   int kpn[Tile<R>::L];
-  const int ep[3] = {e0, e1, e2};
-#pragma unroll
-  for (int j = 0; j < 3; ++j) {
-    if (j < n) {
-      fetch_pos<R, PERM>(kpn, ks, ep[j] & 0xffff);
-      fetch_block<R>(regs, ks, kpn);
-      stage_block<R>(stg[j], regs, tid);
-    }
+  {
+    BlockRegs<R> r0, r1;
+    int kp0[Tile<R>::L], kp1[Tile<R>::L], kp2[Tile<R>::L], kp3[Tile<R>::L];
+    fetch_pos<R, PERM>(kp0, ks, e0 & 0xffff);
+    fetch_pos<R, PERM>(kp1, ks, e1 & 0xffff);
+    fetch_pos<R, PERM>(kp2, ks, e2 & 0xffff);
+    fetch_pos<R, PERM>(kp3, ks, e3 & 0xffff);
+    fetch_pos<R, PERM>(kpn, ks, e4 & 0xffff);
+    fetch_block<R>(r0, ks, kp0);
+    fetch_block<R>(r1, ks, kp1);
+    fetch_block<R>(regs, ks, kp2);
+    load_q();
+    stage_block<R>(stg[0], r0, tid);
+    if (n > 1) stage_block<R>(stg[1], r1, tid);
+    if (n > 2) stage_block<R>(stg[2], regs, tid);
+    fetch_block<R>(regs, ks, kp3);
   }
-  if (n > 3) {
-    fetch_pos<R, PERM>(kpn, ks, e3 & 0xffff);
-    fetch_block<R>(regs, ks, kpn);
-  }
-  if (n > 4) fetch_pos<R, PERM>(kpn, ks, e4 & 0xffff);
   __syncthreads();
 
   f32x16 sa[2], sb[2];
@@ -495,14 +530,55 @@ __device__ __forceinline__ void block_loop(WaveState& ws, Stage* stg, const Attn
   }
 }
 
+// Next work item for a workgroup whose XCD is `home`: the items of that XCD's
+// list in order, then what is left of the others' lists (-1: none; *from: the
+// list it comes from). Counters of one launch, each on its own 128-byte line:
+// per list the entries taken and the entries finished (padding entries count
+// as both), then the workgroups that are through. They only grow, so the
+// search ends.
+__device__ __forceinline__ int take_item(const AttnArgs& a, int home, int* from) {
+#pragma unroll 1
+  for (int x = 0; x < 8; ++x) {
+    const int q = (home + x) & 7;
+#pragma unroll 1
+    for (;;) {
+      const int k = atomicAdd(&a.queue[q * QUEUE_LINE], 1);
+      if (k >= a.map_len) break;
+      const int it = ld_global(a.item_map + q * a.map_len + k);
+      int* done = &a.queue[(8 + q) * QUEUE_LINE];
+      if (it < 0) {
+        atomicAdd(done, 1);
+        continue;
+      }
+      // the workgroups of an XCD start a run of such items together: its
+      // items read much the same keys in the same order, and find them in L2
+      // only while they walk side by side. Bounded by the item's own length,
+      // whatever the other workgroups do.
+      const int lead = load_item(a, it).lead;
+      if (lead > 0) {
+        const int need = k / a.map_run * a.map_run - LEAD_SLACK;
+        const uint64_t budget = (uint64_t)lead * LEAD_TICKS, t0 = __builtin_readsteadycounter();
+        while (__hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need &&
+               __builtin_readsteadycounter() - t0 < budget)
+          __builtin_amdgcn_s_sleep(32);
+      }
+      *from = q;
+      return it;
+    }
+  }
+  return -1;
+}
+
 template <int R, bool WL>
-__global__ __launch_bounds__(128 * R) __attribute__((amdgpu_waves_per_eu(R == 4 ? 2 : 1))) void k_attention(AttnArgs a) {
-  __shared__ Stage stg[NSTAGE];
-  const int64_t it = item_of_block(a, blockIdx.x);
-  if (it < 0 || it >= a.nitems) return;
-  const WorkItem w = a.items[it];
-  const HeadDev hd = a.heads[w.head];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+__device__ __forceinline__ void attend_item(const AttnArgs& a, int it, Stage* stg, int* sh_item) {   // sh_item: item, list
+  const WorkItem w = load_item(a, it);
+  const ItemHead hd = load_head(a, w.head);
+  // opaque, so that what derives from it is not kept in registers across items
+  int tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  const int wave = tid >> 6, lane = tid & 63;
+  EntryStream es;
+  es.init(hd.gcol + w.e0, w.e1 - w.e0, lane);
   // Waves 0..R-1 own rows 0-31 of member `wave`; waves R..2R-1 own rows
   // 32-63 of member (wave - R + R/2) mod R, so that the two waves sharing a
   // SIMD (wave and wave + 4 for R = 4) serve different members.
@@ -513,14 +589,17 @@ __global__ __launch_bounds__(128 * R) __attribute__((amdgpu_waves_per_eu(R == 4 
   const int half = upper ? 1 : 0;
   ws.c = lane & 31;
   ws.h = lane >> 5;
-  const int qblk = group_row(w.group, ws.rb, R, hd.gp[0]);
+  const int qblk = group_row(w.group, ws.rb, R, hd.rho);
   ws.qpos = qblk < hd.nbq ? slot_pos(hd.qperm, qblk * B + half * 32 + ws.c, a.S) : -1;
-  {
+  auto load_q = [&]() {
     const uint16_t* qb = reinterpret_cast<const uint16_t*>(a.q.p) + (int64_t)w.head * a.q.sh;
     const uint16_t* row = qb + (int64_t)max(ws.qpos, 0) * a.q.ss + ws.h * 64;
+    bf16x8 x[8];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) ws.qr[s] = ws.qpos >= 0 ? load16(row + 8 * s) : zero8();
-  }
+    for (int s = 0; s < 8; ++s) x[s] = load16(row + 8 * s);
+#pragma unroll
+    for (int s = 0; s < 8; ++s) ws.qr[s] = ws.qpos >= 0 ? x[s] : zero8();
+  };
   // transpose-read source row/column of this lane inside a V stage
   const int grp = lane >> 4, li = lane & 15;
   ws.vlane = (4 * (grp >> 1) + (li >> 2)) * VPITCH + 16 * (grp & 1) + 4 * (li & 3);
@@ -531,10 +610,22 @@ __global__ __launch_bounds__(128 * R) __attribute__((amdgpu_waves_per_eu(R == 4 
   ws.m = NEG_BIG;
   ws.l = 0.0f;
   ws.lo = 0.0f;
-  if (!hd.causal) block_loop<R, true, false, WL>(ws, stg, a, hd, w, tid);
-  else if (hd.kperm) block_loop<R, true, true, WL>(ws, stg, a, hd, w, tid);
-  else block_loop<R, false, true, WL>(ws, stg, a, hd, w, tid);
+  if (!hd.causal) block_loop<R, true, false, WL>(ws, stg, a, hd, w, es, tid, load_q);
+  else if (hd.kperm) block_loop<R, true, true, WL>(ws, stg, a, hd, w, es, tid, load_q);
+  else block_loop<R, false, true, WL>(ws, stg, a, hd, w, es, tid, load_q);
 
+  if (tid == 0) {                                // under the stores of this item
+    int home = blockIdx.x & 7;
+    asm volatile("" : "+v"(home));               // no addresses kept in registers across items
+    if (a.queue) {
+      atomicAdd(&a.queue[(8 + sh_item[1]) * QUEUE_LINE], 1);
+      int from = 0;
+      sh_item[0] = take_item(a, home, &from);
+      sh_item[1] = from;
+    } else {
+      sh_item[0] = -1;
+    }
+  }
   const float m = ws.m, l = ws.l;
   const int qpos = ws.qpos, h = ws.h;
   // every live row has its own key, so lo > 0 unless this part of a split
@@ -571,6 +662,38 @@ __global__ __launch_bounds__(128 * R) __attribute__((amdgpu_waves_per_eu(R == 4 
       ml[1] = ws.lo;
       ml[2] = WL ? l : 0.0f;
     }
+  }
+}
+
+// Workgroups are persistent: one per CU, each taking items until none is
+// left. One workgroup per item (a.queue null, which graph capture uses) left a
+// CU idle for 10-30 us between items (launch, 152 KB of LDS, then the item's
+// own chain of loads) and an XCD with a lighter list idle at the end: over
+// 256 CUs the items' own time was 93% of the launch at 119K neighborhood
+// attention, 92% at 256K, 85% at 32K. One workgroup per item against this on
+// one box: 119K neighborhood 8787 -> 8417 us, 256K 27666 -> 26436, 128K 54.4
+// -> 53.2 ms, 32K 2811 -> 2568 us, dense 34K 9114 -> 8888.
+template <int R, bool WL>
+__global__ __launch_bounds__(128 * R) __attribute__((amdgpu_waves_per_eu(R == 4 ? 2 : 1))) void k_attention(AttnArgs a) {
+  __shared__ Stage stg[NSTAGE];
+  __shared__ int sh_item[2];
+  if (threadIdx.x == 0) {
+    int from = 0;
+    sh_item[0] = a.queue ? take_item(a, blockIdx.x & 7, &from) : item_of_block(a, blockIdx.x);
+    sh_item[1] = from;
+  }
+  __syncthreads();
+  for (;;) {
+    const int it = __builtin_amdgcn_readfirstlane(sh_item[0]);
+    if (it < 0) break;
+    attend_item<R, WL>(a, it, stg, sh_item);
+    __syncthreads();
+  }
+  if (!a.queue) return;
+  // the last workgroup clears the counters for the next launch of this queue
+  if (threadIdx.x == 0 && atomicAdd(&a.queue[16 * QUEUE_LINE], 1) == (int)gridDim.x - 1) {
+    for (int q = 0; q <= 16; ++q)
+      __hip_atomic_store(&a.queue[q * QUEUE_LINE], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -623,7 +746,7 @@ __global__ __launch_bounds__(256) void k_combine(AttnArgs a, const SplitRow* spl
 
 hipError_t launch_attention(const AttnArgs& a, hipStream_t st) {
   if (a.nitems <= 0) return hipSuccess;
-  const int64_t grid = 8 * a.map_len;
+  const int64_t all = 8 * a.map_len, grid = a.queue ? (all < a.cus ? all : a.cus) : all;
   const bool wl = a.lse != nullptr;      // the fp32-P row sums only when the LSE is asked for
   switch (a.R * 2 + (wl ? 1 : 0)) {
     case 2: hipLaunchKernelGGL((k_attention<1, false>), dim3((unsigned)grid), dim3(128), 0, st, a); break;

@@ -13,14 +13,15 @@
 //   blocks in an LDS bitmap with closed-form rules (ranges, per-block
 //   threshold tests, slash offsets), then stores the bitmap and its
 //   popcount. Bit setting is an OR, so the result is order independent.
-// k_group_count / k_group_fill: the union of the key-block sets of R
+// k_group_eval / k_group_fill: the union of the key-block sets of R
 //   query blocks (a row group), with a per-query-block flag on every entry
 //   (the attention kernel loads each key block once for all R query blocks).
-// k_blocks_scan: per head, prefix sums of counts (CSR row pointers), of the
-//   group unions and of work-item counts.
+// k_blocks_scan: per head, the row-group stride, prefix sums of counts (CSR
+//   row pointers), of the group unions and of work-item counts.
 // k_blocks_fill: ascending column lists from the bitmaps.
-// k_work_fill: work items (a row group and <= chunk union entries each) and
-//   the split-group table for the combine kernel.
+// k_work_fill: work items (a row group and a range of its union entries each)
+//   and the split-group table for the combine kernel.
+// k_item_map: the work items of each XCD, in order.
 #include "device.hpp"
 #include "internal.hpp"
 
@@ -231,9 +232,12 @@ __device__ void qb_grid_rules(uint32_t* bm, const OpDev& op, int sig, int ph, in
   __syncthreads();
 }
 
-__global__ __launch_bounds__(256) void k_blocks_count(const HeadDev* heads, const OpDev* ops, Groups g) {
+// cand: the union totals of the row-stride candidates, cleared here for the
+// pass that follows.
+__global__ __launch_bounds__(256) void k_blocks_count(const HeadDev* heads, const OpDev* ops, Groups g, int64_t* cand) {
   const HeadDev hd = heads[blockIdx.x];
   const int qb = blockIdx.y;
+  if (qb == 0 && threadIdx.x < NRHO) cand[(int64_t)blockIdx.x * NRHO + threadIdx.x] = 0;
   if (qb >= hd.nbq) return;
   __shared__ uint32_t bm[MMI_MAX_SEQ / B / 32 + 8];   // + one block per padded group
   __shared__ int rpos[B], rc[B], ra[B], rb[B];
@@ -334,9 +338,9 @@ __global__ __launch_bounds__(256) void k_blocks_count(const HeadDev* heads, cons
 }
 
 hipError_t launch_blocks_count(const HeadDev* heads, int nheads, const OpDev* ops, Groups g, int max_nbq,
-                               hipStream_t st) {
+                               int64_t* cand, hipStream_t st) {
   if (nheads <= 0 || max_nbq <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_blocks_count, dim3(nheads, max_nbq), dim3(256), 0, st, heads, ops, g);
+  hipLaunchKernelGGL(k_blocks_count, dim3(nheads, max_nbq), dim3(256), 0, st, heads, ops, g, cand);
   return hipGetLastError();
 }
 
@@ -352,11 +356,6 @@ __device__ int union_count(const HeadDev& hd, int g, int R, int rho) {
     cnt += __popc(u);
   }
   return cnt;
-}
-
-__global__ void k_zero64(int64_t* p, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
 }
 
 // Candidate row strides: 1, 2, 4, 8 and the head's extra ones (0 = none).
@@ -433,22 +432,9 @@ __global__ __launch_bounds__(256) void k_group_eval4(const HeadDev* heads, int64
   }
 }
 
-__global__ void k_group_pick(const HeadDev* heads, int nheads, int R, const int64_t* cand) {
-  const int h = blockIdx.x * blockDim.x + threadIdx.x;
-  if (h >= nheads) return;
-  const HeadDev hd = heads[h];
-  int best = 0;
-  for (int c = 1; c < NRHO; ++c)
-    if (rho_candidate(hd, c) > 0 && cand[h * NRHO + c] < cand[h * NRHO + best]) best = c;
-  hd.gp[0] = rho_candidate(hd, best);
-  hd.gp[1] = groups_for(hd.nbq, R, hd.gp[0]);
-  hd.gp[2] = best;
-}
-
 hipError_t launch_group_stride(const HeadDev* heads, int nheads, int R, int max_groups, int max_nbq, bool extra,
                                int64_t* cand, int32_t* gcnt, hipStream_t st) {
   if (nheads <= 0 || max_groups <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_zero64, dim3((nheads * NRHO + 255) / 256), dim3(256), 0, st, cand, nheads * NRHO);
   if (R == 4) {
     hipLaunchKernelGGL(k_group_eval4, dim3(nheads, (max_nbq + 31) / 32), dim3(256), 0, st, heads, cand, gcnt,
                        max_groups);
@@ -457,106 +443,123 @@ hipError_t launch_group_stride(const HeadDev* heads, int nheads, int R, int max_
   } else {
     hipLaunchKernelGGL(k_group_eval, dim3(nheads, max_groups), dim3(256), 0, st, heads, R, cand, gcnt, max_groups, 0);
   }
-  hipLaunchKernelGGL(k_group_pick, dim3((nheads + 63) / 64), dim3(64), 0, st, heads, nheads, R, cand);
-  return hipGetLastError();
-}
-
-// The chosen stride's union sizes (counted by k_group_eval).
-__global__ __launch_bounds__(256) void k_group_count(const HeadDev* heads, const int32_t* gcnt, int max_groups) {
-  const HeadDev hd = heads[blockIdx.x];
-  const int gr = blockIdx.y * 256 + threadIdx.x;
-  if (gr >= hd.gp[1]) return;
-  hd.gcount[gr] = gcnt[((int64_t)blockIdx.x * NRHO + hd.gp[2]) * max_groups + gr];
-}
-
-hipError_t launch_group_count(const HeadDev* heads, int nheads, const int32_t* gcnt, int max_groups,
-                              hipStream_t st) {
-  if (nheads <= 0 || max_groups <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_group_count, dim3(nheads, (max_groups + 255) / 256), dim3(256), 0, st, heads, gcnt,
-                     max_groups);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- scans
 constexpr int SCAN_T = 1024;
+constexpr int SCAN_W = SCAN_T / 64;
 
-// exclusive block scan of one int per thread; returns the block total
-__device__ int block_exscan(int v, int* buf, int& excl) {
-  const int tid = threadIdx.x;
-  buf[tid] = v;
-  __syncthreads();
-  for (int off = 1; off < SCAN_T; off <<= 1) {
-    const int t = tid >= off ? buf[tid - off] : 0;
-    __syncthreads();
-    buf[tid] += t;
-    __syncthreads();
+// Exclusive prefix sums over the workgroup of N ints per thread, in thread
+// order (wave shuffles, then the wave totals through LDS); tot: the sums of
+// all. Two barriers whatever N is.
+template <int N>
+__device__ __forceinline__ void block_exscan(const int (&v)[N], int (&excl)[N], int (&tot)[N], int (*buf)[SCAN_W]) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int s[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    s[k] = v[k];
+    for (int off = 1; off < 64; off <<= 1) {
+      const int t = __shfl_up(s[k], off, 64);
+      if (lane >= off) s[k] += t;
+    }
+    if (lane == 63) buf[k][wave] = s[k];
   }
-  excl = buf[tid] - v;
-  const int tot = buf[SCAN_T - 1];
   __syncthreads();
-  return tot;
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    int pre = 0, all = 0;
+    for (int w = 0; w < SCAN_W; ++w) {
+      pre += w < wave ? buf[k][w] : 0;
+      all += buf[k][w];
+    }
+    excl[k] = pre + s[k] - v[k];
+    tot[k] = all;
+  }
+  __syncthreads();
 }
 
-__global__ __launch_bounds__(SCAN_T) void k_blocks_scan(const HeadDev* heads, int min_chunk, int items_per_head,
-                                                        int avg_factor, int64_t* totals) {
+// Candidate of the smallest total union of a head (ties to the earlier one).
+__device__ __forceinline__ int best_rho(const HeadDev& hd, const int64_t* cand) {
+  int best = 0;
+  for (int c = 1; c < NRHO; ++c)
+    if (rho_candidate(hd, c) > 0 && cand[c] < cand[best]) best = c;
+  return best;
+}
+
+// One workgroup per head: the row stride, CSR row pointers, group offsets and
+// work-item counts. A split row group writes and reads 131 KB of fp32
+// partials per part, and its parts share no key blocks with their neighbours
+// on the XCD, so a union is split only beyond both of
+//   a 1 / items share of the whole layer's staged blocks (items = 512: half of
+//   what one of 256 CUs gets; the shares of all heads are added from cand).
+//   32K layer, attention + merge: 2743 us, 3147 with 1024 items, 3025 with
+//   4096; dense 34K 8793 us against 9740 with 2048; 128K 54.2 ms against 59.6
+//   with 4096; with per-head shares of 8192 items 3341 us, 10664 us, 55.5 ms;
+//   three times the layer's average union, 16 to 64 entries: in a layer too short
+//   to fill the chip the longest union is the critical path, and where the
+//   others are short its parts are few (4K tokens, 2 Grid heads: attention +
+//   merge 126 us unsplit, 58 with 24 entries, 50 with 16; 8K, 8 Grid heads:
+//   141, 71, 66); where they are as long (3,001 tokens, 28 heads: 127, 127,
+//   132) the parts cost what the shorter path gives.
+__global__ __launch_bounds__(SCAN_T) void k_blocks_scan(const HeadDev* heads, int nheads, int R, const int64_t* cand,
+                                                        const int32_t* gcnt, int max_groups, int min_chunk, int items,
+                                                        int all_groups, int64_t* totals) {
   const HeadDev hd = heads[blockIdx.x];
-  __shared__ int buf[SCAN_T];
+  __shared__ int buf[1][SCAN_W];
+  __shared__ unsigned long long sh_all;
+  if (threadIdx.x == 0) sh_all = 0;
+  __syncthreads();
+  for (int h = threadIdx.x; h < nheads; h += SCAN_T)
+    atomicAdd(&sh_all, (unsigned long long)cand[(int64_t)h * NRHO + best_rho(heads[h], cand + (int64_t)h * NRHO)]);
+  const int best = best_rho(hd, cand + (int64_t)blockIdx.x * NRHO);
+  const int rho = rho_candidate(hd, best), ngroups = groups_for(hd.nbq, R, rho);
+  const int32_t* gsize = gcnt + ((int64_t)blockIdx.x * NRHO + best) * max_groups;
+  __syncthreads();
+  const int64_t share = ((int64_t)sh_all + items - 1) / items;
+  const int floor = min_chunk > 0 ? min_chunk : min(64, max(16, 3 * (int)((int64_t)sh_all / all_groups)));
+  const int chunk = (int)min<int64_t>(INT_BIG / 2, max<int64_t>(floor, share));
   int c_nnz = 0;
   for (int start = 0; start < hd.nbq; start += SCAN_T) {
     const int i = start + threadIdx.x;
-    const int cnt = i < hd.nbq ? hd.counts[i] : 0;
-    int e0;
-    const int t0 = block_exscan(cnt, buf, e0);
-    if (i < hd.nbq) hd.rowptr[i] = c_nnz + e0;
-    c_nnz += t0;
+    int v[1] = {i < hd.nbq ? hd.counts[i] : 0}, e[1], t[1];
+    block_exscan<1>(v, e, t, buf);
+    if (i < hd.nbq) hd.rowptr[i] = c_nnz + e[0];
+    c_nnz += t[0];
   }
-  const int ngroups = hd.gp[1];
-  int c_g = 0;
+  int c_g = 0, c_items = 0, c_split = 0, c_parts = 0;
+  __shared__ int buf4[4][SCAN_W];
   for (int start = 0; start < ngroups; start += SCAN_T) {
     const int i = start + threadIdx.x;
-    const int cnt = i < ngroups ? hd.gcount[i] : 0;
-    int e0;
-    const int t0 = block_exscan(cnt, buf, e0);
-    if (i < ngroups) hd.growptr[i] = c_g + e0;
-    c_g += t0;
-  }
-  // long unions are split so that no work item holds much more than a
-  // 1/items_per_head share of the head's work
-  int chunk = max(min_chunk, (int)(((int64_t)c_g + items_per_head - 1) / items_per_head));
-  if (avg_factor > 0 && ngroups > 0)
-    chunk = max(chunk, (int)min<int64_t>(INT_BIG, (int64_t)avg_factor * (((int64_t)c_g + ngroups - 1) / ngroups)));
-  int c_items = 0, c_split = 0, c_parts = 0;
-  for (int start = 0; start < ngroups; start += SCAN_T) {
-    const int i = start + threadIdx.x;
-    const int ch = i < ngroups ? (hd.gcount[i] + chunk - 1) / chunk : 0;
-    const int sp = ch > 1 ? 1 : 0;
-    const int pt = ch > 1 ? ch : 0;
-    int e1, e2, e3;
-    const int t1 = block_exscan(ch, buf, e1);
-    const int t2 = block_exscan(sp, buf, e2);
-    const int t3 = block_exscan(pt, buf, e3);
+    const int cnt = i < ngroups ? gsize[i] : 0;
+    const int ch = (cnt + chunk - 1) / chunk;
+    int v[4] = {cnt, ch, ch > 1 ? 1 : 0, ch > 1 ? ch : 0}, e[4], t[4];
+    block_exscan<4>(v, e, t, buf4);
     if (i < ngroups) {
+      hd.growptr[i] = c_g + e[0];
       hd.chunks[i] = ch;
-      hd.itembase[i] = c_items + e1;
-      hd.splitoff[i] = c_split + e2;
-      hd.partoff[i] = c_parts + e3;
+      hd.itembase[i] = c_items + e[1];
+      hd.splitoff[i] = c_split + e[2];
+      hd.partoff[i] = c_parts + e[3];
     }
-    c_items += t1; c_split += t2; c_parts += t3;
+    c_g += t[0]; c_items += t[1]; c_split += t[2]; c_parts += t[3];
   }
   if (threadIdx.x == 0) {
+    hd.gp[0] = rho;
+    hd.gp[1] = ngroups;
     hd.rowptr[hd.nbq] = c_nnz;
     hd.growptr[ngroups] = c_g;
-    hd.chunklen[0] = chunk;
     int64_t* t = totals + (int64_t)blockIdx.x * NTOT;
     t[0] = c_nnz; t[1] = c_g; t[2] = c_items; t[3] = c_split; t[4] = c_parts;
   }
 }
 
-hipError_t launch_blocks_scan(const HeadDev* heads, int nheads, int min_chunk, int items_per_head,
-                              int avg_factor, int64_t* totals, hipStream_t st) {
+hipError_t launch_blocks_scan(const HeadDev* heads, int nheads, int R, const int64_t* cand, const int32_t* gcnt,
+                              int max_groups, int min_chunk, int items, int all_groups, int64_t* totals, hipStream_t st) {
   if (nheads <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_blocks_scan, dim3(nheads), dim3(SCAN_T), 0, st, heads, min_chunk, items_per_head, avg_factor,
-                     totals);
+  hipLaunchKernelGGL(k_blocks_scan, dim3(nheads), dim3(SCAN_T), 0, st, heads, nheads, R, cand, gcnt, max_groups,
+                     min_chunk, items, all_groups, totals);
   return hipGetLastError();
 }
 
@@ -705,28 +708,52 @@ hipError_t launch_blocks_fill(const HeadDev* heads, int nheads, int max_nbq, int
   return hipGetLastError();
 }
 
-__global__ __launch_bounds__(256) void k_work_fill(const HeadDev* heads, const int64_t* item_base,
+// Cost weights of an item: a staged K/V block costs about 1.5 computed blocks
+// (the attention kernel's time fitted over the 1M workloads: 2.6 ms per million
+// staged blocks, 1.75 ms per million computed blocks).
+constexpr float COST_STAGE = 1.5f, COST_COMPUTE = 1.0f;
+
+// Items whose workgroups start side by side (WorkItem::lead): those of heads
+// with at least RUN_KEYS key blocks, whose K and V (32 KB a block) outgrow the
+// 256 MB last-level cache, so that reading them apart costs HBM reads, and
+// with walks long enough to lose each other. 1M layer: attention 588 ms with
+// it, 655 without (the same workgroups free-running); 128K and 256K layers,
+// whose K/V fit the cache, lose 1-2% to the waiting.
+constexpr int RUN_KEYS = 8192, RUN_STEPS = 256;
+
+// Work items of every row group: nparts equal ranges of its union, with their
+// modelled cost (an item takes its share of the group's computed blocks).
+__global__ __launch_bounds__(256) void k_work_fill(const HeadDev* heads, int R, const int64_t* item_base,
                                                    const int64_t* part_base, const int64_t* split_base,
-                                                   WorkItem* items, SplitRow* splits) {
+                                                   WorkItem* items, float* cost, SplitRow* splits) {
   const int h = blockIdx.x;
   const HeadDev hd = heads[h];
   const int gr = blockIdx.y * 256 + threadIdx.x;
   if (gr >= hd.gp[1]) return;
-  const int chunk = hd.chunklen[0];
   const int nch = hd.chunks[gr];
+  if (nch <= 0) return;
   const int r0 = hd.growptr[gr], r1 = hd.growptr[gr + 1];
+  const int len = (r1 - r0 + nch - 1) / nch;
   const int64_t ib = item_base[h] + hd.itembase[gr];
   const bool split = nch > 1;
   const int64_t pb = part_base[h] + hd.partoff[gr];
+  int computed = 0;
+  for (int r = 0; r < R; ++r) {
+    const int row = group_row(gr, r, R, hd.gp[0]);
+    if (row < hd.nbq) computed += hd.counts[row];
+  }
+  const float per = COST_STAGE + COST_COMPUTE * (float)computed / (float)(r1 - r0);
   for (int c = 0; c < nch; ++c) {
     WorkItem w;
     w.head = h;
     w.group = gr;
-    w.e0 = r0 + c * chunk;
-    w.e1 = min(r0 + (c + 1) * chunk, r1);
+    w.e0 = r0 + c * len;
+    w.e1 = min(r0 + (c + 1) * len, r1);
     w.part = split ? (int)(pb + c) : -1;
-    w.pad[0] = w.pad[1] = w.pad[2] = 0;
+    w.lead = hd.nbk >= RUN_KEYS && w.e1 - w.e0 >= RUN_STEPS ? w.e1 - w.e0 : 0;
+    w.pad[0] = w.pad[1] = 0;
     items[ib + c] = w;
+    cost[ib + c] = per * (float)(w.e1 - w.e0);
   }
   if (split) {
     SplitRow s;
@@ -738,42 +765,95 @@ __global__ __launch_bounds__(256) void k_work_fill(const HeadDev* heads, const i
   }
 }
 
-// Cost weights: a staged K/V block costs about 1.5 computed blocks (the
-// attention kernel's time fitted over the 1M workloads: 2.6 ms per million
-// staged blocks, 1.75 ms per million computed blocks).
-constexpr float COST_STAGE = 1.5f, COST_COMPUTE = 1.0f;
+// Item map: items (row groups, or parts of long ones, in head and group
+// order) are cut into runs of consecutive items, which share key blocks; the
+// runs are dealt to the 8 XCDs in order of their longest item, each to the
+// XCD with the least cost so far that still has a free run slot, and each XCD
+// runs its runs in that order. Longest item first: what an XCD starts last is
+// then short (ordered by the runs' sums, a run with one long group started
+// late: with static lists 32K layer attention 3417 us against 3095, dense 34K
+// 9396 against 8789). One workgroup: the runs are sorted in LDS (bitonic) and dealt by one
+// wave, a dozen instructions per run, in place of a copy to the host, a sort
+// there and a copy back between the two halves of the plan.
+constexpr int MAP_T = 1024;
 
-// One wave per item: sum over its union entries of the staged block and the
-// computed blocks (select flags, bits 16-23).
-__global__ __launch_bounds__(256) void k_item_cost(const HeadDev* heads, const WorkItem* items, int64_t nitems,
-                                                   float* cost) {
-  const int64_t it = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (it >= nitems) return;
-  const int lane = threadIdx.x & 63;
-  const WorkItem w = items[it];
-  const int32_t* g = heads[w.head].gcol;
-  float acc = 0.0f;
-  for (int e = w.e0 + lane; e < w.e1; e += 64)
-    acc += COST_STAGE + COST_COMPUTE * (float)__popc(((uint32_t)g[e] >> 16) & 0xffu);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
-  if (lane == 0) cost[it] = acc;
+__device__ __forceinline__ uint32_t min8(uint32_t x) {   // smallest of each 8 lanes, in all of them
+  x = min(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xf, 0xf, true));    // lane ^ 1
+  x = min(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x4E, 0xf, 0xf, true));    // lane ^ 2
+  return min(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0x141, 0xf, 0xf, true));  // mirrored in 8 lanes
 }
 
-hipError_t launch_item_cost(const HeadDev* heads, const WorkItem* items, int64_t nitems, float* cost,
-                            hipStream_t st) {
-  if (nitems <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_item_cost, dim3((unsigned)((nitems + 3) / 4)), dim3(256), 0, st, heads, items, nitems,
-                     cost);
+__global__ __launch_bounds__(MAP_T) void k_item_map(const float* cost, int64_t n, MapShape m, int32_t* map,
+                                                    int32_t* queues, int nqueues) {
+  __shared__ uint64_t key[MAP_RUNS];          // longest item (fp32 bits) above, ~run below: sorted descending
+  __shared__ float sum[MAP_RUNS];
+  __shared__ int32_t run_at[8 * MAP_CAP];     // run of each (XCD, slot), -1 = none
+  const int tid = threadIdx.x;
+  for (int x = tid; x < nqueues * QUEUE_INTS; x += MAP_T) queues[x] = 0;
+  int n2 = 1;
+  while (n2 < m.nruns) n2 <<= 1;
+  for (int j = tid; j < n2; j += MAP_T) {
+    float mx = 0.0f, s = 0.0f;
+    if (j < m.nruns)
+      for (int64_t i = (int64_t)j * m.run; i < min(n, (int64_t)(j + 1) * m.run); ++i) {
+        mx = fmaxf(mx, cost[i]);
+        s += cost[i];
+      }
+    key[j] = j < m.nruns ? ((uint64_t)__float_as_uint(mx) << 32) | (0xffffffffu - (uint32_t)j) : 0;
+    sum[j] = s;
+  }
+  for (int x = tid; x < 8 * m.cap; x += MAP_T) run_at[x] = -1;
+  __syncthreads();
+  for (int k = 2; k <= n2; k <<= 1)
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      for (int i = tid; i < n2; i += MAP_T) {
+        const int p = i ^ j;
+        if (p > i) {
+          const uint64_t x = key[i], y = key[p];
+          if ((x < y) == ((i & k) == 0)) { key[i] = y; key[p] = x; }
+        }
+      }
+      __syncthreads();
+    }
+  if (tid < 64) {
+    // lane x < 8 holds XCD x: cost so far (non-negative, so its bits order like
+    // the value) and runs taken; the lanes above repeat them
+    float load = 0.0f;
+    int taken = 0;
+    const int xcd = tid & 7;
+    for (int s = 0; s < m.nruns; ++s) {
+      const int j = (int)(0xffffffffu - (uint32_t)key[s]);
+      const uint32_t c = taken < m.cap ? __float_as_uint(load) : 0xffffffffu;
+      const uint64_t first = __ballot(c == min8(c)) & 0xffu;
+      if (xcd == __ffsll((unsigned long long)first) - 1) {
+        if (tid < 8) run_at[xcd * m.cap + taken] = j;
+        load += sum[j];
+        ++taken;
+      }
+    }
+  }
+  __syncthreads();
+  const int64_t len = m.cap * m.run;
+  for (int64_t x = tid; x < 8 * len; x += MAP_T) {
+    const int j = run_at[x / len * m.cap + x % len / m.run];
+    const int64_t i = (int64_t)j * m.run + x % m.run;     // len is a multiple of run
+    map[x] = j >= 0 && i < n ? (int32_t)i : -1;
+  }
+}
+
+hipError_t launch_item_map(const float* cost, int64_t n, int32_t* map, int32_t* queues, int nqueues, hipStream_t st) {
+  if (n <= 0) return hipSuccess;
+  hipLaunchKernelGGL(k_item_map, dim3(1), dim3(MAP_T), 0, st, cost, n, map_shape(n), map,
+                     queues, nqueues);
   return hipGetLastError();
 }
 
-hipError_t launch_work_fill(const HeadDev* heads, int nheads, const int64_t* item_base,
+hipError_t launch_work_fill(const HeadDev* heads, int nheads, int R, const int64_t* item_base,
                             const int64_t* part_base, const int64_t* split_base, int max_groups,
-                            WorkItem* items, SplitRow* splits, hipStream_t st) {
+                            WorkItem* items, float* cost, SplitRow* splits, hipStream_t st) {
   if (nheads <= 0 || max_groups <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_work_fill, dim3(nheads, (max_groups + 255) / 256), dim3(256), 0, st, heads, item_base,
-                     part_base, split_base, items, splits);
+  hipLaunchKernelGGL(k_work_fill, dim3(nheads, (max_groups + 255) / 256), dim3(256), 0, st, heads, R, item_base,
+                     part_base, split_base, items, cost, splits);
   return hipGetLastError();
 }
 

@@ -119,10 +119,9 @@ static void scratch_setup(int device) {              // device is current
 
 struct mmi_ctx {
   int device = 0;
-  int chunk_blocks = 64;           // smallest work-item length (union entries)
-  int items_per_layer = 8192;      // target number of work items per layer
-  int split_above_avg = 6;         // with enough row groups, split only groups above this many times
-                                   // their head's average union (0: always split to the item target)
+  int chunk_blocks = 0;            // unions up to this many entries are never split (0: by the layer's average)
+  int items_per_layer = 512;       // unions up to this share of the layer's staged blocks are never split
+  int cus = 256;                   // compute units, rounded down to a multiple of 8
   int row_group = 4;               // query blocks per attention work item (1, 2 or 4)
   int live_plans = 0;              // plans created from this context and not destroyed
   bool debug = false;              // MMI_DEBUG: check every plan's tables, synchronise every execute
@@ -163,6 +162,8 @@ struct HostHead {
 
 }  // namespace mmi
 
+constexpr size_t NQUEUES = 8;      // streams of one plan whose launches are persistent
+
 struct mmi_plan {
   mmi_ctx* ctx = nullptr;
   hipStream_t stream = nullptr;
@@ -182,6 +183,8 @@ struct mmi_plan {
   int64_t nitems = 0, nsplit = 0, nparts = 0;
   int32_t* d_item_map = nullptr;  // [8][map_len] work items per XCD
   int64_t map_len = 0;
+  int32_t* d_queues = nullptr;    // [NQUEUES][QUEUE_INTS] item counters of the attention launches
+  std::vector<hipStream_t> queue_of;  // stream that uses queue i
   int R = 1;                      // query blocks per attention work item
   int32_t* d_tpos = nullptr;
   std::vector<uint8_t> mod;       // host modality of every position (all 0 without a layout)
@@ -529,8 +532,6 @@ static void validate_inputs(const mmi_problem* prob, const mmi_head_cfg* cfgs, c
   validate_cfgs(L.g, p, cfgs);
 }
 
-static void build_item_map(mmi_plan* P, hipStream_t st);
-
 static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi_head_cfg* cfgs, const void* q,
                              const void* k, hipStream_t st, mmi_plan* P) {
   const mmi_problem p = normalise(prob_in);
@@ -768,10 +769,8 @@ static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi
     }
     const int max_rho = std::max(8, std::max(hd.rho_alt[0], hd.rho_alt[1]));
     hd.gcap = (hd.nbq + R - 1) / R + max_rho;   // >= groups_for(nbq, R, rho) for every candidate
-    hd.gp = dalloc<int32_t>(P, 3);
-    hd.gcount = dalloc<int32_t>(P, hd.gcap);
+    hd.gp = dalloc<int32_t>(P, 2);
     hd.growptr = dalloc<int32_t>(P, hd.gcap + 1);
-    hd.chunklen = dalloc<int32_t>(P, 1);
     hd.chunks = dalloc<int32_t>(P, hd.gcap);
     hd.itembase = dalloc<int32_t>(P, hd.gcap);
     hd.splitoff = dalloc<int32_t>(P, hd.gcap);
@@ -849,25 +848,19 @@ static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi
   HIPCHK(launch_perms(P->d_heads, p.Hq, P->d_ops, g, bd.d_tpos, S, max_slots, st));
   HIPCHK(launch_qb_order(d_qj, (int)qjobs.size(), d_modpos, S, st));
   HIPCHK(launch_key_summaries(P->d_heads, p.Hq, P->d_ops, (int)P->ops.size(), g, max_nbk, bd.max_sel, st));
-  const int chunk = ctx->chunk_blocks;
-  HIPCHK(launch_blocks_count(P->d_heads, p.Hq, P->d_ops, g, max_nbq, st));
   int64_t* d_cand = dalloc<int64_t>(P, (size_t)p.Hq * NRHO);
+  HIPCHK(launch_blocks_count(P->d_heads, p.Hq, P->d_ops, g, max_nbq, d_cand, st));
   int32_t* d_gcnt = dalloc<int32_t>(P, (size_t)p.Hq * NRHO * std::max(max_groups, 1));
   bool extra_rho = false;
   for (const HeadDev& hd : P->heads) extra_rho = extra_rho || hd.rho_alt[0] > 0 || hd.rho_alt[1] > 0;
   HIPCHK(launch_group_stride(P->d_heads, p.Hq, R, max_groups, max_nbq, extra_rho, d_cand, d_gcnt, st));
-  HIPCHK(launch_group_count(P->d_heads, p.Hq, d_gcnt, max_groups, st));
   const size_t ntot = (size_t)p.Hq * NTOT;
+  int64_t ngroups = 0;
+  for (const HeadDev& hd : P->heads) ngroups += (hd.nbq + R - 1) / R;
+  const int all_groups = (int)std::min<int64_t>(std::max<int64_t>(ngroups, 1), INT_BIG);
   int64_t* d_tot = dalloc<int64_t>(P, ntot);
-  const int items_per_head = std::max(1, ctx->items_per_layer / p.Hq);
-  // When the row groups alone already give the target number of work items,
-  // only groups far above their head's average are split (a split puts
-  // chunks of one union side by side on an XCD, which share no key blocks,
-  // in place of neighbouring groups, which do).
-  int64_t groups_all = 0;
-  for (const auto& hd : P->heads) groups_all += (hd.nbq + R - 1) / R;
-  const int split_above_avg = groups_all >= ctx->items_per_layer ? ctx->split_above_avg : 0;
-  HIPCHK(launch_blocks_scan(P->d_heads, p.Hq, chunk, items_per_head, split_above_avg, d_tot, st));
+  HIPCHK(launch_blocks_scan(P->d_heads, p.Hq, R, d_cand, d_gcnt, max_groups, ctx->chunk_blocks, ctx->items_per_layer,
+                            all_groups, d_tot, st));
   std::vector<int64_t> tot_host;
   const int64_t* tot = nullptr;
   if (P->scratch) {                      // pageable host copy: no pinned allocation
@@ -917,76 +910,30 @@ static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi
     off += P->hh[h].nnz;
     goff += P->hh[h].gnnz;
   }
-  P->keep.emplace_back(reinterpret_cast<const uint8_t*>(P->heads.data()),
-                       reinterpret_cast<const uint8_t*>(P->heads.data()) + sizeof(HeadDev) * p.Hq);
-  HIPCHK(hipMemcpyAsync(P->d_heads, P->keep.back().data(), sizeof(HeadDev) * p.Hq, hipMemcpyHostToDevice, st));
-  HIPCHK(launch_blocks_fill(P->d_heads, p.Hq, max_nbq, R, max_groups, st));
-  P->d_items = dalloc<WorkItem>(P, P->nitems);
-  P->d_splits = dalloc<SplitRow>(P, P->nsplit);
-  P->d_part_o = dalloc<float>(P, (size_t)std::max<int64_t>(P->nparts, 1) * B * R * D);
-  P->d_part_ml = dalloc<float>(P, (size_t)std::max<int64_t>(P->nparts, 1) * B * R * 4);
   int64_t *d_ib = nullptr, *d_pb = nullptr, *d_sb = nullptr;
   {
     Pack pk;
+    pk.add(P->heads, P->d_heads);
     pk.add(item_base, d_ib);
     pk.add(part_base, d_pb);
     pk.add(split_base, d_sb);
     send(P, pk);
   }
-  HIPCHK(launch_work_fill(P->d_heads, p.Hq, d_ib, d_pb, d_sb, max_groups, P->d_items, P->d_splits, st));
-  build_item_map(P, st);
+  HIPCHK(launch_blocks_fill(P->d_heads, p.Hq, max_nbq, R, max_groups, st));
+  P->d_items = dalloc<WorkItem>(P, P->nitems);
+  P->d_splits = dalloc<SplitRow>(P, P->nsplit);
+  P->d_part_o = dalloc<float>(P, (size_t)P->nparts * B * R * D);
+  P->d_part_ml = dalloc<float>(P, (size_t)P->nparts * B * R * 4);
+  float* d_cost = dalloc<float>(P, P->nitems);
+  HIPCHK(launch_work_fill(P->d_heads, p.Hq, R, d_ib, d_pb, d_sb, max_groups, P->d_items, d_cost, P->d_splits, st));
+  const MapShape ms = map_shape(P->nitems);
+  P->map_len = P->nitems > 0 ? (int64_t)ms.cap * ms.run : 0;
+  P->d_item_map = dalloc<int32_t>(P, (size_t)8 * P->map_len);
+  P->d_queues = dalloc<int32_t>(P, (size_t)NQUEUES * QUEUE_INTS);
+  HIPCHK(launch_item_map(d_cost, P->nitems, P->d_item_map, P->d_queues, NQUEUES, st));
   mark(P, 3, st);
   P->nnz_all = nnz_all;
   P->gnnz_all = gnnz_all;
-}
-
-// Work items of each XCD. Items (row groups, or chunks of long ones, in head
-// and group order) are cut into runs of consecutive items, which share key
-// blocks; the runs are dealt to the 8 XCDs longest first, each to the XCD
-// with the least modelled cost so far (at most a quarter more runs than the
-// average per XCD), and each XCD runs its runs in that order. Runs are 32
-// items, fewer for small layers so that every XCD gets some.
-static void build_item_map(mmi_plan* P, hipStream_t st) {
-  const int64_t n = P->nitems;
-  if (n <= 0) return;
-  float* d_cost = dalloc<float>(P, n);
-  HIPCHK(launch_item_cost(P->d_heads, P->d_items, n, d_cost, st));
-  std::vector<float> cost(n);
-  HIPCHK(hipMemcpyAsync(cost.data(), d_cost, sizeof(float) * n, hipMemcpyDeviceToHost, st));
-  HIPCHK(hipStreamSynchronize(st));
-  const int64_t run = std::max<int64_t>(1, std::min<int64_t>(32, n / 64));
-  const int64_t nruns = (n + run - 1) / run;
-  std::vector<double> rc(nruns, 0.0);
-  for (int64_t i = 0; i < n; ++i) rc[i / run] += cost[i];
-  std::vector<int64_t> order(nruns);
-  for (int64_t j = 0; j < nruns; ++j) order[j] = j;
-  std::stable_sort(order.begin(), order.end(), [&](int64_t x, int64_t y) { return rc[x] > rc[y]; });
-  const int64_t avg = (nruns + 7) / 8, cap = avg + std::max<int64_t>(1, avg / 4);
-  double load[8] = {0};
-  std::vector<int64_t> runs_of[8];
-  for (int64_t j : order) {
-    int best = -1;
-    for (int x = 0; x < 8; ++x)
-      if ((int64_t)runs_of[x].size() < cap && (best < 0 || load[x] < load[best])) best = x;
-    runs_of[best].push_back(j);
-    load[best] += rc[j];
-  }
-  int64_t len = 0;
-  std::vector<int64_t> items_of(8, 0);
-  for (int x = 0; x < 8; ++x) {
-    for (int64_t j : runs_of[x]) items_of[x] += std::min(run, n - j * run);
-    len = std::max(len, items_of[x]);
-  }
-  std::vector<int32_t> map((size_t)8 * len, -1);
-  for (int x = 0; x < 8; ++x) {
-    int64_t k = 0;
-    for (int64_t j : runs_of[x])
-      for (int64_t i = j * run; i < std::min(n, (j + 1) * run); ++i) map[(size_t)x * len + k++] = (int32_t)i;
-  }
-  Pack pk;
-  pk.add(map, P->d_item_map);
-  send(P, pk);
-  P->map_len = len;
 }
 
 // What mmi_plan_stats takes from the device, for every head of the plan (the
@@ -1036,7 +983,7 @@ static void plan_check(mmi_plan* P) {
   for (int h = 0; h < P->Hq; ++h) {
     const HeadDev& hd = P->heads[h];
     const HostHead& H = P->hh[h];
-    const std::vector<int32_t> gp = get(hd.gp, 3);
+    const std::vector<int32_t> gp = get(hd.gp, 2);
     if (gp[0] < 1 || gp[1] < 0 || gp[1] > hd.gcap)
       fail(MMI_ERR_INTERNAL, "plan check, head %d: row stride %d, %d row groups (capacity %d)", h, gp[0], gp[1],
            hd.gcap);
@@ -1100,6 +1047,28 @@ static void plan_check(mmi_plan* P) {
   if (!e.empty()) fail(MMI_ERR_INTERNAL, "plan check, work list: %s", e.c_str());
 }
 
+// Item counters of an execute on stream st: launches on one stream follow
+// each other, so each stream the plan runs on gets a set of its own (their
+// last launch leaves it cleared). A captured launch may be replayed beside
+// anything, the per-thread stream is a different one in every thread, and a
+// plan has NQUEUES sets: those launches take one workgroup per item (nullptr).
+static int32_t* queue_for(mmi_plan* P, hipStream_t st) {
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (!P->d_queues || st == hipStreamPerThread) return nullptr;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  if (cap != hipStreamCaptureStatusNone) return nullptr;
+  size_t i = 0;
+  while (i < P->queue_of.size() && P->queue_of[i] != st) ++i;
+  if (i == P->queue_of.size()) {
+    if (i == NQUEUES) return nullptr;
+    P->queue_of.push_back(st);
+  }
+  return P->d_queues + i * QUEUE_INTS;
+}
+
 static void plan_execute_impl(mmi_plan* P, const void* q, const void* k, const void* v, void* o, float* lse,
                               hipStream_t st) {
   if (!q || !k || !v || !o) fail(MMI_ERR_INVALID_ARG, "q/k/v/o is NULL");
@@ -1121,7 +1090,10 @@ static void plan_execute_impl(mmi_plan* P, const void* q, const void* k, const v
   a.part_ml = P->d_part_ml;
   a.item_map = P->d_item_map;
   a.map_len = P->map_len;
+  a.map_run = map_shape(P->nitems).run;
   a.R = P->R;
+  a.queue = queue_for(P, st);
+  a.cus = P->ctx->cus;
   mark(P, 4, st);
   HIPCHK(launch_attention(a, st));
   mark(P, 5, st);
@@ -1186,6 +1158,9 @@ int mmi_ctx_create(int device, mmi_ctx** out) {
     scratch_setup(device);
     auto* c = new mmi_ctx();
     c->device = device;
+    int cus = 0;
+    HIPCHK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device));
+    c->cus = std::max(8, cus / 8 * 8);
     if (const char* e = getenv("MMI_CHUNK_BLOCKS")) {
       const int v = atoi(e);
       if (v >= 1) c->chunk_blocks = v;
@@ -1193,10 +1168,6 @@ int mmi_ctx_create(int device, mmi_ctx** out) {
     if (const char* e = getenv("MMI_ITEMS_PER_LAYER")) {
       const int v = atoi(e);
       if (v >= 1) c->items_per_layer = v;
-    }
-    if (const char* e = getenv("MMI_SPLIT_ABOVE_AVG")) {
-      const int v = atoi(e);
-      if (v >= 0) c->split_above_avg = v;
     }
     if (const char* e = getenv("MMI_DEBUG")) c->debug = e[0] != '\0' && strcmp(e, "0") != 0;
     if (const char* e = getenv("MMI_ROW_GROUP")) {

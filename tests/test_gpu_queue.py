@@ -1,0 +1,85 @@
+"""The attention launch's item queue: streams, capture, few and many items (needs an MI355X)."""
+import pytest
+import torch
+
+from synth import config as C
+
+pytestmark = pytest.mark.gpu
+
+
+def _layer(S, Hq, Hkv, seed):
+    g = torch.Generator().manual_seed(seed)
+    return [torch.randn(S, h, 128, generator=g).to(torch.bfloat16).cuda() for h in (Hq, Hkv, Hkv)]
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2504_16083_amd import mmi
+    c = mmi.Ctx(0)
+    yield c
+    c.close()
+
+
+def test_streams_share_a_plan(ctx):
+    """One plan on more streams than it has queues, launches in flight together: every output bitwise the first."""
+    from paper_2504_16083_amd import mmi
+    print("[gpu] queue streams", flush=True)
+    S = 5000
+    q, k, v = _layer(S, 8, 2, 1)
+    heads = [C.global_head(C.dense()), C.global_head(C.grid(40, 60)), C.global_head(C.ashape(64, 500)),
+             C.global_head(C.vslash(100, 50))] * 2
+    plan = mmi.Plan(ctx, mmi.Problem(S, 8, 2, None), heads, q, k)
+    want = torch.empty_like(q)
+    plan.execute(q, k, v, want)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(11)]
+    outs = [torch.full_like(q, 7.0) for _ in range(33)]
+    torch.cuda.synchronize()
+    for i, o in enumerate(outs):
+        plan.execute(q, k, v, o, None, streams[i % 11])
+    torch.cuda.synchronize()
+    for i, o in enumerate(outs):
+        assert torch.equal(o, want), i
+    plan.destroy()
+
+
+def test_graph_replay(ctx):
+    """A captured execute replayed between eager ones on new inputs."""
+    from paper_2504_16083_amd import mmi
+    print("[gpu] queue capture", flush=True)
+    S = 3000
+    q, k, v = _layer(S, 4, 2, 2)
+    plan = mmi.Plan(ctx, mmi.Problem(S, 4, 2, None), [C.global_head(C.ashape(64, 300))] * 4, q, k)
+    o, e = torch.zeros_like(q), torch.zeros_like(q)
+    plan.execute(q, k, v, e)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        plan.execute(q, k, v, o)
+    for i in range(3):
+        v.copy_(_layer(S, 4, 2, 10 + i)[2])
+        plan.execute(q, k, v, e)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(o, e), i
+    plan.destroy()
+
+
+@pytest.mark.parametrize("S,Hq", [(1, 1), (64, 1), (257, 1), (300, 9), (2048, 40)])
+def test_item_counts(ctx, S, Hq):
+    """From one item to more than the CUs: rows all written, the plan's tables consistent."""
+    from paper_2504_16083_amd import mmi
+    print(f"[gpu] queue items S={S} Hq={Hq}", flush=True)
+    q, k, v = _layer(S, Hq, 1, 3)
+    plan = mmi.Plan(ctx, mmi.Problem(S, Hq, 1, None), [C.global_head(C.dense())] * Hq, q, k)
+    plan.check()
+    o = torch.full_like(q, float("nan"))
+    for _ in range(2):
+        plan.execute(q, k, v, o)
+    torch.cuda.synchronize()
+    plan.destroy()
+    a = torch.einsum("qhd,kd->hqk", q.float().cpu(), k[:, 0].float().cpu()) / 128 ** 0.5
+    a.masked_fill_(torch.ones(S, S).triu_(1).bool(), float("-inf"))
+    want = torch.einsum("hqk,kd->qhd", a.softmax(-1), v[:, 0].float().cpu())
+    # the output bound of the parity tests: 2e-2 plus half a bf16 spacing (|O| < 8 here: 2^-6)
+    assert (o.float().cpu() - want).abs().max() <= 2e-2 + 2.0 ** -6
