@@ -106,7 +106,6 @@ struct HeadDev {
   int32_t* rowptr;            // [nbq+1]
   uint32_t* bitmap;           // [nbq][nwords]
   int32_t nwords;
-  int32_t* col;               // [nnz]
   int32_t op0;                // first OpDev of this head
   // Row groups: R query blocks processed by one work item over the union of
   // their key lists (entries: key block | flags << 16, bit r of the flags =
@@ -197,7 +196,9 @@ hipError_t launch_group_stride(const HeadDev* heads, int nheads, int R, int max_
 constexpr int NTOT = 5;
 hipError_t launch_blocks_scan(const HeadDev* heads, int nheads, int R, const int64_t* cand, const int32_t* gcnt,
                               int max_groups, int min_chunk, int items, int all_groups, int64_t* totals, hipStream_t st);
-hipError_t launch_blocks_fill(const HeadDev* heads, int nheads, int max_nbq, int R, int max_groups,
+hipError_t launch_group_fill(const HeadDev* heads, int nheads, int R, int max_groups, int max_nbk, hipStream_t st);
+// the column lists of every head: head h's at col + col_off[h]
+hipError_t launch_blocks_fill(const HeadDev* heads, int nheads, int max_nbq, const int64_t* col_off, int32_t* col,
                               hipStream_t st);
 // Runs of consecutive work items and their slots in the item map ([8][cap *
 // run], -1 = none): 32 items per run, fewer for small layers so that every XCD

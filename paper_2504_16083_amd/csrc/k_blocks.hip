@@ -332,7 +332,8 @@ __global__ __launch_bounds__(256) void k_blocks_count(const HeadDev* heads, cons
     gbm[w] = v;
     cnt += __popc(v);
   }
-  atomicAdd(&sh_count, cnt);
+  for (int off = 32; off > 0; off >>= 1) cnt += __shfl_xor(cnt, off, 64);
+  if ((tid & 63) == 0) atomicAdd(&sh_count, cnt);
   __syncthreads();
   if (tid == 0) hd.counts[qb] = sh_count;
 }
@@ -340,7 +341,12 @@ __global__ __launch_bounds__(256) void k_blocks_count(const HeadDev* heads, cons
 hipError_t launch_blocks_count(const HeadDev* heads, int nheads, const OpDev* ops, Groups g, int max_nbq,
                                int64_t* cand, hipStream_t st) {
   if (nheads <= 0 || max_nbq <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_blocks_count, dim3(nheads, max_nbq), dim3(256), 0, st, heads, ops, g, cand);
+  // a chain of dependent loads and barriers per query block: one wave each once
+  // there are enough of them to fill the chip (256K layer, 131K blocks: the
+  // stage 580 us shorter than with four waves each), four for the few of a
+  // short layer
+  const int nt = (int64_t)nheads * max_nbq >= 2048 ? 64 : 256;
+  hipLaunchKernelGGL(k_blocks_count, dim3(nheads, max_nbq), dim3(nt), 0, st, heads, ops, g, cand);
   return hipGetLastError();
 }
 
@@ -567,9 +573,10 @@ hipError_t launch_blocks_scan(const HeadDev* heads, int nheads, int R, const int
 // words (one padding block per modality group), so 256 threads need 5.
 constexpr int GF_WORDS = 5;
 
-// Exclusive prefix sum of one count per thread over a 256-thread workgroup,
-// in thread order (wave shuffles, then the wave totals through LDS);
+// Exclusive prefix sum of one count per thread over a workgroup of NT
+// threads, in thread order (wave shuffles, then the wave totals through LDS);
 // *total receives the sum of all.
+template <int NT>
 __device__ __forceinline__ int block_exclusive_scan(int cnt, int* wtot, int* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int s = cnt;
@@ -580,7 +587,7 @@ __device__ __forceinline__ int block_exclusive_scan(int cnt, int* wtot, int* tot
   if (lane == 63) wtot[wave] = s;
   __syncthreads();
   int pre = 0, tot = 0;
-  for (int v = 0; v < 4; ++v) {
+  for (int v = 0; v < NT / 64; ++v) {
     if (v < wave) pre += wtot[v];
     tot += wtot[v];
   }
@@ -589,8 +596,11 @@ __device__ __forceinline__ int block_exclusive_scan(int cnt, int* wtot, int* tot
 }
 
 // Ascending column list of one query block from its bitmap (each thread's
-// words read once, kept in registers for the write).
-__global__ __launch_bounds__(256) void k_blocks_fill(const HeadDev* heads) {
+// words read once, kept in registers for the write): col + col_off[head] +
+// rowptr. The attention reads row-group unions; only an export or a check of
+// the index asks for these lists, so a plan makes them then (they took 200 us
+// of a 128K layer's index, 1.1 ms at 1M).
+__global__ __launch_bounds__(256) void k_blocks_fill(const HeadDev* heads, const int64_t* col_off, int32_t* col) {
   const HeadDev hd = heads[blockIdx.x];
   const int qb = blockIdx.y;
   if (qb >= hd.nbq) return;
@@ -606,13 +616,14 @@ __global__ __launch_bounds__(256) void k_blocks_fill(const HeadDev* heads) {
     cnt += __popc(x[k]);
   }
   int total;
-  int pos = hd.rowptr[qb] + block_exclusive_scan(cnt, wtot, &total);
+  int32_t* out = col + col_off[blockIdx.x];
+  int pos = hd.rowptr[qb] + block_exclusive_scan<256>(cnt, wtot, &total);
 #pragma unroll
   for (int k = 0; k < GF_WORDS; ++k) {
     uint32_t v = x[k];
     while (v) {
       const int b = __ffs(v) - 1;
-      hd.col[pos++] = (w0 + k) * 32 + b;
+      out[pos++] = (w0 + k) * 32 + b;
       v &= v - 1;
     }
   }
@@ -625,8 +636,11 @@ __global__ __launch_bounds__(256) void k_blocks_fill(const HeadDev* heads) {
 // bits 0-15, bit 16+r set if query block r of the group selects it, bit 24+r
 // set if it does and the key block holds a position above the smallest
 // query position of query block r (or padding), i.e. needs the causal mask
-// (for a bidirectional head: only if the key block holds padding).
-__global__ __launch_bounds__(256) void k_group_fill(const HeadDev* heads, int R) {
+// (for a bidirectional head: only if the key block holds padding). NT threads:
+// one wave while its lanes hold a bitmap row (GF_WORDS words each: 10,240 key
+// blocks), four waves for longer rows.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_group_fill(const HeadDev* heads, int R) {
   const HeadDev hd = heads[blockIdx.x];
   const int gr = blockIdx.y;
   if (gr >= hd.gp[1]) return;
@@ -645,7 +659,7 @@ __global__ __launch_bounds__(256) void k_group_fill(const HeadDev* heads, int R)
     if (p >= 0) atomicMin(&qmin[r], hd.causal ? p : INT_BIG - 1);   // bidirectional: only padding masks
   }
   // this thread's words of the members' bitmaps, read once for both passes
-  const int per = (hd.nwords + 255) / 256;
+  const int per = (hd.nwords + NT - 1) / NT;
   const int w0 = threadIdx.x * per;
   uint32_t bits[GF_WORDS][4];
   int cntA = 0, cntB = 0;        // entries every member selects / the others
@@ -666,8 +680,8 @@ __global__ __launch_bounds__(256) void k_group_fill(const HeadDev* heads, int R)
   }
   // exclusive prefix sums of both counts over the workgroup in thread order
   int totA, totB;
-  const int preA = block_exclusive_scan(cntA, wtot[0], &totA);
-  const int preB = block_exclusive_scan(cntB, wtot[1], &totB);
+  const int preA = block_exclusive_scan<NT>(cntA, wtot[0], &totA);
+  const int preB = block_exclusive_scan<NT>(cntB, wtot[1], &totB);
   int posA = hd.growptr[gr] + preA;
   int posB = hd.growptr[gr] + totA + preB;
 #pragma unroll
@@ -700,11 +714,19 @@ __global__ __launch_bounds__(256) void k_group_fill(const HeadDev* heads, int R)
   }
 }
 
-hipError_t launch_blocks_fill(const HeadDev* heads, int nheads, int max_nbq, int R, int max_groups,
+hipError_t launch_blocks_fill(const HeadDev* heads, int nheads, int max_nbq, const int64_t* col_off, int32_t* col,
                               hipStream_t st) {
   if (nheads <= 0 || max_nbq <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_blocks_fill, dim3(nheads, max_nbq), dim3(256), 0, st, heads);
-  hipLaunchKernelGGL(k_group_fill, dim3(nheads, max_groups), dim3(256), 0, st, heads, R);
+  hipLaunchKernelGGL(k_blocks_fill, dim3(nheads, max_nbq), dim3(256), 0, st, heads, col_off, col);
+  return hipGetLastError();
+}
+
+hipError_t launch_group_fill(const HeadDev* heads, int nheads, int R, int max_groups, int max_nbk, hipStream_t st) {
+  if (nheads <= 0 || max_groups <= 0) return hipSuccess;
+  if (max_nbk <= 64 * GF_WORDS * 32)
+    hipLaunchKernelGGL(k_group_fill<64>, dim3(nheads, max_groups), dim3(64), 0, st, heads, R);
+  else
+    hipLaunchKernelGGL(k_group_fill<256>, dim3(nheads, max_groups), dim3(256), 0, st, heads, R);
   return hipGetLastError();
 }
 

@@ -62,8 +62,8 @@ __device__ __forceinline__ int block_modality(const int32_t* perm, const uint8_t
 }
 
 // Workgroup = (head, STAT_ROWS query blocks). The modalities of the head's
-// key blocks go to LDS first; each wave then walks the columns of a query
-// block at a time, a counter per key modality.
+// key blocks go to LDS first; each wave then walks the bitmap of a query block
+// at a time, a counter per key modality.
 constexpr int STAT_ROWS = 64;
 
 __global__ __launch_bounds__(256) void k_head_stats(const HeadDev* heads, const OpDev* ops, const int32_t* op_slot,
@@ -93,11 +93,12 @@ __global__ __launch_bounds__(256) void k_head_stats(const HeadDev* heads, const 
     const int mq = block_modality(hd.qperm, mod, qb, hd.S);
     if (mq < 0) continue;
     int c[MMI_MAX_MODALITIES] = {};
-    for (int e = hd.rowptr[qb] + lane; e < hd.rowptr[qb + 1]; e += 64) {
-      const int mk = kmod[hd.col[e]];
+    for (int w = lane; w < hd.nwords; w += 64)
+      for (uint32_t v = hd.bitmap[(int64_t)qb * hd.nwords + w]; v; v &= v - 1) {
+        const int mk = kmod[w * 32 + __ffs(v) - 1];
 #pragma unroll
-      for (int m = 0; m < MMI_MAX_MODALITIES; ++m) c[m] += mk == m ? 1 : 0;
-    }
+        for (int m = 0; m < MMI_MAX_MODALITIES; ++m) c[m] += mk == m ? 1 : 0;
+      }
 #pragma unroll
     for (int m = 0; m < MMI_MAX_MODALITIES; ++m) {
       for (int off = 32; off > 0; off >>= 1) c[m] += __shfl_xor(c[m], off, 64);

@@ -195,6 +195,7 @@ struct mmi_plan {
   int64_t gnnz_all = 0;
   bool executed = false;
   std::vector<int> rowset_n;
+  std::vector<int32_t*> col;      // column lists of the heads, once asked for
   std::vector<mmi::HeadStatDev> stats;   // of every head, filled by the first mmi_plan_stats
   int64_t device_bytes = 0;       // device memory the plan holds
   uint8_t* scratch = nullptr;     // non-null: buffers come from the no-allocation scratch
@@ -419,7 +420,7 @@ struct Builder {
     j.u = need_u ? dalloc<float>(P, L_c) : nullptr;
     j.dpart = need_u ? dalloc<float>(P, (size_t)j.ntiles * 128) : nullptr;
     max_tiles = std::max(max_tiles, j.ntiles);
-    max_L = std::max(max_L, L_c);
+    if (need_u) max_L = std::max(max_L, L_c);
     e.job = (int)jobs.size();
     e.L_c = L_c; e.nrows = nrows; e.row0 = row0;
     e.v = j.v; e.u = j.u;
@@ -561,17 +562,20 @@ static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi
   for (int gi = 0; gi < g.n; ++gi) toff_by_mod[g.mod[gi]] = g.toff[gi];
   Segment* d_segs = nullptr;
   int32_t* d_toff = nullptr;
-  {
+  bool qb_grid = false, boundary = false;       // only boundary heads read the position lists
+  for (int h = 0; h < p.Hq; ++h) {
+    boundary |= cfgs[h].kind != MMI_HEAD_GLOBAL;
+    qb_grid |= cfgs[h].kind == MMI_HEAD_QBOUNDARY && qb_grid_mods(g, cfgs[h]) > 0;
+  }
+  uint8_t* d_modpos = qb_grid ? dalloc<uint8_t>(P, S) : nullptr;
+  if (boundary) {
     Pack pk;
     pk.add(L.segs, d_segs);
     pk.add(toff_by_mod, d_toff);
     send(P, pk);
+    bd.d_tpos = P->d_tpos = dalloc<int32_t>(P, S);
+    HIPCHK(launch_positions(d_segs, (int)L.segs.size(), d_toff, bd.d_tpos, d_modpos, S, st));
   }
-  bd.d_tpos = P->d_tpos = dalloc<int32_t>(P, S);
-  bool qb_grid = false;
-  for (int h = 0; h < p.Hq; ++h) qb_grid |= cfgs[h].kind == MMI_HEAD_QBOUNDARY && qb_grid_mods(g, cfgs[h]) > 0;
-  uint8_t* d_modpos = qb_grid ? dalloc<uint8_t>(P, S) : nullptr;
-  HIPCHK(launch_positions(d_segs, (int)L.segs.size(), d_toff, bd.d_tpos, d_modpos, S, st));
   std::vector<QbOrderJob> qjobs;
 
   const int nb_all = (S + B - 1) / B;
@@ -785,7 +789,7 @@ static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi
   // estimation -> choices
   const Tensor tq{q, p.q_stride_s, p.q_stride_h}, tk{k, p.k_stride_s, p.k_stride_h};
   if (!P->scratch)
-    for (auto& e : P->ev) HIPCHK(hipEventCreate(&e));
+    for (auto& e : P->ev) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableSystemFence));   // stage times only
   // members of the estimation groups that read the same keys: row sets per
   // KV head, score jobs per (KV head, key map)
   auto grouped = [](int n, auto key_of, int& ngrp, int& nr) {
@@ -901,13 +905,10 @@ static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi
   }
   if (P->nitems > 0x7fffffff || P->nparts > 0x7fffffff)
     fail(MMI_ERR_UNSUPPORTED, "work list too large (%lld items)", (long long)P->nitems);
-  int32_t* col = dalloc<int32_t>(P, nnz_all);
   int32_t* gcol = dalloc<int32_t>(P, gnnz_all);
-  int64_t off = 0, goff = 0;
+  int64_t goff = 0;
   for (int h = 0; h < p.Hq; ++h) {
-    P->heads[h].col = col + off;
     P->heads[h].gcol = gcol + goff;
-    off += P->hh[h].nnz;
     goff += P->hh[h].gnnz;
   }
   int64_t *d_ib = nullptr, *d_pb = nullptr, *d_sb = nullptr;
@@ -919,7 +920,7 @@ static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi
     pk.add(split_base, d_sb);
     send(P, pk);
   }
-  HIPCHK(launch_blocks_fill(P->d_heads, p.Hq, max_nbq, R, max_groups, st));
+  HIPCHK(launch_group_fill(P->d_heads, p.Hq, R, max_groups, max_nbk, st));
   P->d_items = dalloc<WorkItem>(P, P->nitems);
   P->d_splits = dalloc<SplitRow>(P, P->nsplit);
   P->d_part_o = dalloc<float>(P, (size_t)P->nparts * B * R * D);
@@ -967,11 +968,36 @@ static std::vector<HeadStatDev> read_stats(mmi_plan* P) {
   return out;
 }
 
+// Column lists of every head, made when first asked for (exports, checks):
+// head h's start at plan->col[h].
+static void make_columns(mmi_plan* P) {
+  if (!P->col.empty()) return;
+  std::vector<int64_t> off(P->Hq);
+  int64_t n = 0;
+  int max_nbq = 0;
+  for (int h = 0; h < P->Hq; ++h) {
+    off[h] = n;
+    n += P->hh[h].nnz;
+    max_nbq = std::max(max_nbq, P->heads[h].nbq);
+  }
+  int64_t* d_off = nullptr;
+  {
+    Pack pk;
+    pk.add(off, d_off);
+    send(P, pk);
+  }
+  int32_t* col = dalloc<int32_t>(P, n);
+  HIPCHK(launch_blocks_fill(P->d_heads, P->Hq, max_nbq, d_off, col, P->stream));
+  HIPCHK(hipStreamSynchronize(P->stream));
+  for (int h = 0; h < P->Hq; ++h) P->col.push_back(col + off[h]);
+}
+
 // The debug check of a plan: its tables copied to the host, each head's
 // block index and row-group unions, then the work list and item map.
 static void plan_check(mmi_plan* P) {
   HIPCHK(hipSetDevice(P->ctx->device));
   HIPCHK(hipStreamSynchronize(P->stream));
+  make_columns(P);
   auto get = [](const int32_t* src, size_t n) {
     std::vector<int32_t> v(std::max<size_t>(n, 1));
     if (n) HIPCHK(hipMemcpy(v.data(), src, n * 4, hipMemcpyDeviceToHost));
@@ -989,7 +1015,7 @@ static void plan_check(mmi_plan* P) {
            hd.gcap);
     const std::vector<int32_t> qp = hd.qperm ? get(hd.qperm, (size_t)hd.nbq * B) : std::vector<int32_t>();
     const std::vector<int32_t> kp = hd.kperm ? get(hd.kperm, (size_t)hd.nbk * B) : std::vector<int32_t>();
-    const std::vector<int32_t> rp = get(hd.rowptr, hd.nbq + 1), col = get(hd.col, H.nnz);
+    const std::vector<int32_t> rp = get(hd.rowptr, hd.nbq + 1), col = get(P->col[h], H.nnz);
     uptr[h] = get(hd.growptr, (size_t)gp[1] + 1);
     const std::vector<int32_t> ent = get(hd.gcol, H.gnnz);
     if (rp[hd.nbq] != H.nnz || uptr[h][gp[1]] != H.gnnz)
@@ -1353,7 +1379,7 @@ int mmi_plan_export(mmi_plan* P, int head, int what, int slot, void* dst, size_t
         break;
       }
       case MMI_EXPORT_ROW_PTR: src = hd.rowptr; n = (size_t)(hd.nbq + 1) * 4; break;
-      case MMI_EXPORT_COL_IDX: src = hd.col; n = (size_t)H.nnz * 4; break;
+      case MMI_EXPORT_COL_IDX: make_columns(P); src = P->col[head]; n = (size_t)H.nnz * 4; break;
       case MMI_EXPORT_V_SCORES: src = e->v; n = e->v ? (size_t)e->L_c * 4 : 0; break;
       case MMI_EXPORT_U_SCORES: src = e->u; n = e->u ? (size_t)e->L_c * 4 : 0; break;
       case MMI_EXPORT_FOLD: src = e->fold; n = e->fold ? (size_t)std::max(0, e->hi - e->lo + 1) * FOLD_W * 4 : 0; break;
