@@ -473,15 +473,18 @@ __device__ __forceinline__ void block_exscan(const int (&v)[N], int (&excl)[N], 
     if (lane == 63) buf[k][wave] = s[k];
   }
   __syncthreads();
+  // every wave scans the wave totals itself (lanes 0 .. SCAN_W - 1)
 #pragma unroll
   for (int k = 0; k < N; ++k) {
-    int pre = 0, all = 0;
-    for (int w = 0; w < SCAN_W; ++w) {
-      pre += w < wave ? buf[k][w] : 0;
-      all += buf[k][w];
+    int x = lane < SCAN_W ? buf[k][lane] : 0;
+#pragma unroll
+    for (int off = 1; off < SCAN_W; off <<= 1) {
+      const int t = __shfl_up(x, off, 64);
+      if (lane >= off) x += t;
     }
-    excl[k] = pre + s[k] - v[k];
-    tot[k] = all;
+    const int pre = __shfl(x, max(wave - 1, 0), 64);
+    excl[k] = (wave > 0 ? pre : 0) + s[k] - v[k];
+    tot[k] = __shfl(x, SCAN_W - 1, 64);
   }
   __syncthreads();
 }
@@ -797,7 +800,7 @@ __global__ __launch_bounds__(256) void k_work_fill(const HeadDev* heads, int R, 
 // 9396 against 8789). One workgroup: the runs are sorted in LDS (bitonic) and dealt by one
 // wave, a dozen instructions per run, in place of a copy to the host, a sort
 // there and a copy back between the two halves of the plan.
-constexpr int MAP_T = 1024;
+constexpr int MAP_T = 256;
 
 __device__ __forceinline__ uint32_t min8(uint32_t x) {   // smallest of each 8 lanes, in all of them
   x = min(x, (uint32_t)__builtin_amdgcn_mov_dpp((int)x, 0xB1, 0xf, 0xf, true));    // lane ^ 1
@@ -843,22 +846,28 @@ __global__ __launch_bounds__(MAP_T) void k_item_map(const float* cost, int64_t n
     float load = 0.0f;
     int taken = 0;
     const int xcd = tid & 7;
-    for (int s = 0; s < m.nruns; ++s) {
-      const int j = (int)(0xffffffffu - (uint32_t)key[s]);
-      const uint32_t c = taken < m.cap ? __float_as_uint(load) : 0xffffffffu;
-      const uint64_t first = __ballot(c == min8(c)) & 0xffu;
-      if (xcd == __ffsll((unsigned long long)first) - 1) {
-        if (tid < 8) run_at[xcd * m.cap + taken] = j;
-        load += sum[j];
-        ++taken;
+    for (int s0 = 0; s0 < m.nruns; s0 += 64) {
+      const int sl = min(s0 + tid, m.nruns - 1);         // 64 runs at a time in registers
+      const int run = (int)(0xffffffffu - (uint32_t)key[sl]);
+      const float cost_of = sum[run];
+      for (int i = 0; i < min(64, m.nruns - s0); ++i) {
+        const float rc = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(cost_of), i));
+        const uint32_t c = taken < m.cap ? __float_as_uint(load) : 0xffffffffu;
+        const uint64_t first = __ballot(c == min8(c)) & 0xffu;
+        if (xcd == __ffsll((unsigned long long)first) - 1) {
+          if (tid < 8) run_at[xcd * m.cap + taken] = __builtin_amdgcn_readlane(run, i);
+          load += rc;
+          ++taken;
+        }
       }
     }
   }
   __syncthreads();
-  const int64_t len = m.cap * m.run;
-  for (int64_t x = tid; x < 8 * len; x += MAP_T) {
-    const int j = run_at[x / len * m.cap + x % len / m.run];
-    const int64_t i = (int64_t)j * m.run + x % m.run;     // len is a multiple of run
+  const uint32_t all = 8u * m.cap * m.run;      // below 2^32: there are at most 2^31 items
+  for (uint32_t x = tid; x < all; x += MAP_T) {
+    const uint32_t slot = x / m.run;
+    const int j = run_at[slot];
+    const int64_t i = (int64_t)j * m.run + (x - slot * m.run);
     map[x] = j >= 0 && i < n ? (int32_t)i : -1;
   }
 }
