@@ -76,15 +76,21 @@ __host__ __device__ inline int grid_g0(const GridGeo& g, int phase) {
   return grid_g0_rank(g, grid_rank(g, phase));
 }
 
-// coordinate held by slot x in [0, L)
+// coordinate held by slot x in [0, L): the ranks come in four stretches of
+// equal group size (phases p+1 .. s-1, those below R first; then 0 .. p, again
+// those below R first), so one division finds the group. (A binary search
+// over the ranks, two divisions a step, took the permutation passes of a 66K
+// Q-Boundary Grid layer 90 us.)
 __host__ __device__ inline int grid_coord(const GridGeo& g, int x) {
-  int lo = 0, hi = g.s - 1;      // largest rank with g0_rank(rank) <= x
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (grid_g0_rank(g, mid) <= x) lo = mid; else hi = mid - 1;
-  }
-  int phase = (g.p + 1 + lo) % g.s;
-  return (x - grid_g0_rank(g, lo)) * g.s + phase;
+  const int a = max(0, g.R - g.p - 1), n1 = g.s - 1 - g.p, b = min(g.R, g.p + 1);
+  const int t1 = a * (g.A + 1), t2 = t1 + (n1 - a) * g.A, t3 = t2 + b * (g.A + 1);
+  const bool wide = x < t1 || (x >= t2 && x < t3);          // groups of A + 1
+  const int first = x < t1 ? 0 : x < t2 ? a : x < t3 ? n1 : n1 + b;
+  const int y = x - (x < t1 ? 0 : x < t2 ? t1 : x < t3 ? t2 : t3), len = g.A + (wide ? 1 : 0);
+  const int k = y / len;
+  int phase = g.p + 1 + first + k;
+  if (phase >= g.s) phase -= g.s;
+  return (y - k * len) * g.s + phase;
 }
 
 // slot holding coordinate c
