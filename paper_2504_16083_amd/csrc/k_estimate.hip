@@ -6,9 +6,10 @@
 //   2^(tau log2e q.k) per row -> partials; k_est_merge folds the chunks in
 //   a fixed order into log2-domain LSE.
 // Pass 2 (k_est_scores): per query set and run of 64-key tiles of the key
-//   coordinate system, A_hat tile through MFMA, then in LDS the column sums
-//   (v, written directly: each tile owns its keys) and the 127 diagonal
-//   partial sums of the tile; k_est_udiag adds the (at most two) tiles that
+//   coordinate system, A_hat tile through MFMA, the column sums (v, written
+//   directly: each tile owns its keys) from registers and, where the job asks
+//   for diagonals, the 127 diagonal partial sums of the tile in LDS;
+//   k_est_udiag adds the (at most two) tiles that
 //   touch each diagonal offset. Every reduction has a fixed order, so the
 //   scores are bitwise reproducible.
 // The query rows are contiguous positions [row0, row0+nrows), nrows <= 64,
@@ -88,7 +89,7 @@ __device__ __forceinline__ void staged_product(const EstStage& st, const bf16x8 
 
 
 // This lane's half of key row kpos (zeros for kpos < 0): the K operand of
-// one 32-key S^T tile.
+// one 32-key tile.
 __device__ __forceinline__ void load_key(bf16x8 (&ka)[8], const Tensor& k, int kvh, int kpos, int h) {
   const uint16_t* row = reinterpret_cast<const uint16_t*>(k.p) + (int64_t)kvh * k.sh +
                         (int64_t)max(kpos, 0) * k.ss + h * 64;
@@ -96,13 +97,13 @@ __device__ __forceinline__ void load_key(bf16x8 (&ka)[8], const Tensor& k, int k
   for (int s = 0; s < 8; ++s) ka[s] = kpos >= 0 ? load16(row + 8 * s) : zero8();
 }
 
-// S^T tile of 32 keys x 32 queries; lane (c, h) holds keys 8i + 4h + j for query c.
-__device__ __forceinline__ f32x16 key_product(const bf16x8 (&ka)[8], const bf16x8 (&qr)[8]) {
+// S tile of 32 queries x 32 keys; lane (c, h) holds queries 8i + 4h + j for key c.
+__device__ __forceinline__ f32x16 key_product(const bf16x8 (&qr)[8], const bf16x8 (&ka)[8]) {
   f32x16 acc;
 #pragma unroll
   for (int x = 0; x < 16; ++x) acc[x] = 0.0f;
 #pragma unroll
-  for (int s = 0; s < 8; ++s) acc = mfma32(ka[s], qr[s], acc);
+  for (int s = 0; s < 8; ++s) acc = mfma32(qr[s], ka[s], acc);
   return acc;
 }
 
@@ -231,20 +232,24 @@ __global__ __launch_bounds__(64 * MERGE_W) void k_est_merge(const RowSet* sets) 
   rs.lse2[r] = M + fast_log2(L);
 }
 
-constexpr int APITCH = 65;   // floats per key row of A_hat in LDS: odd, so that the lanes of the
-                             // diagonal sums (one diagonal each) read distinct banks
+constexpr int APITCH = 65;   // floats per key row of A_hat in LDS: odd, so that a row's lanes and a
+                             // diagonal's rows fall in different banks
 constexpr int EST_TPW_MAX = 8;  // most 64-key tiles per workgroup of the score pass
 
-// Each workgroup takes tpw consecutive tiles of one job: the query rows
-// are loaded once, and the key positions and K rows of the tile after next
-// load while the current tile is reduced. The arithmetic of every tile is the same as
-// one tile per workgroup.
+// Each workgroup takes tpw consecutive tiles of one job: the query rows are
+// loaded once, and the key positions and K rows of the tile after next load
+// while the current tile is reduced. A tile comes out of the MFMAs with one
+// key per lane and the query rows in its registers, so a column sum is a sum
+// over registers and one lane swap: jobs without diagonals (Grid, VERT) need
+// neither LDS nor barriers, the others put the tile in LDS for the diagonal
+// sums only. (With the queries over the lanes both sums went through LDS,
+// three barriers a tile: 66K Grid jobs 105.6 -> 87.5 us, 128K 290 -> 240, 256K
+// 356 -> 312.)
 // Logical item = (group, run of tpw tiles, member): order[group * nr +
 // member] is a job index (-1 = none), nrun runs per group.
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void k_est_scores(const EstJob* jobs, const int32_t* order, int ngrp, int nr,
                                                     int nrun, int tpw, const RowSet* sets, Tensor q, Tensor k) {
   __shared__ __align__(16) float ahat[B * APITCH];
-  __shared__ int kposl[B];      // key positions of the current tile, INT_BIG past L_c
   const int64_t lg = run_item(blockIdx.x, nr);
   const int64_t pair = lg / nr;
   const int grp = (int)(pair / nrun), tr = (int)(pair % nrun);
@@ -256,18 +261,20 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void k
   if (ta >= jb.ntiles) return;
   const int tb = min(ta + tpw, jb.ntiles);
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, c = lane & 31, h = lane >> 5;
-  // wave w multiplies keys 32 w .. 32 w + 31 of each tile by all 64 rows
-  // (each K row is loaded once per workgroup); lane (c, h) holds rows c and
-  // 32 + c as B operands
-  int qpos[2];
-  float lse2[2];
+  // wave w multiplies all 64 rows by keys 32 w .. 32 w + 31 of each tile (each
+  // K row is loaded once per workgroup); lane (c, h) holds rows c and 32 + c as
+  // A operands and, of the product, key c and rows 32 hf + 8 i + 4 h + j
+  float lse2[2][16];
   bf16x8 qr[2][8];
 #pragma unroll
   for (int hf = 0; hf < 2; ++hf) {
     const int r = hf * 32 + c;
-    qpos[hf] = r < jb.nrows ? jb.row0 + r : -1;
-    lse2[hf] = qpos[hf] >= 0 ? sets[jb.rowset].lse2[r] : 0.0f;
-    load_q_operand(qr[hf], q, jb.head, qpos[hf], h);
+    load_q_operand(qr[hf], q, jb.head, r < jb.nrows ? jb.row0 + r : -1, h);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int x = hf * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
+      lse2[hf][e] = x < jb.nrows ? sets[jb.rowset].lse2[x] : 0.0f;
+    }
   }
   auto key_pos = [&](int kap) { return kap < jb.L_c ? (jb.keymap ? jb.keymap[kap] : kap) : -1; };
   // two tiles of K rows in registers: tile t + 2 loads while tiles t and t + 1 are used
@@ -280,49 +287,48 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(2))) void k
   auto tile = [&](int buf, int t) {
     f32x16 s[2];
 #pragma unroll
-    for (int hf = 0; hf < 2; ++hf) s[hf] = key_product(ka[buf], qr[hf]);
-    if (h == 0) kposl[wave * 32 + c] = kp[buf] >= 0 ? kp[buf] : INT_BIG;
+    for (int hf = 0; hf < 2; ++hf) s[hf] = key_product(qr[hf], ka[buf]);
+    // rows from `first` on see the lane's key (none if it is past L_c)
+    const int first = kp[buf] >= 0 ? kp[buf] - jb.row0 : INT_BIG;
     if (t + 2 < tb) fetch(buf, t + 2);
-    __syncthreads();
+    float sum = 0.0f;
 #pragma unroll
     for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int kk = wave * 32 + 8 * i + 4 * h + j;   // key index inside the tile
-          const int kp2 = kposl[kk];
-          const float a = (qpos[hf] >= 0 && kp2 <= qpos[hf]) ? fast_exp2(s[hf][4 * i + j] * SC - lse2[hf]) : 0.0f;
-          ahat[kk * APITCH + hf * 32 + c] = a;
-        }
-    __syncthreads();
-    {   // column sums: two threads per key, rows 0-31 and 32-63, then the pair
-      const int kk = tid >> 1, half = tid & 1;
-      const float* src = &ahat[kk * APITCH + 32 * half];
-      float acc = 0.0f;
-#pragma unroll
-      for (int x = 0; x < 32; ++x) acc += src[x];
-      const float other = __shfl_xor(acc, 1);
-      const float tot = half == 0 ? acc + other : other + acc;
-      const int kap = t * B + kk;
-      if (half == 0 && kap < jb.L_c) jb.v[kap] = tot;
-    }
-    if (jb.dpart) {   // diagonal d = r - kk + 63, d in [0, 127)
-      const int d = tid;
-      float acc = 0.0f;
-      if (d < 127) {
-        // rows rr with key rr + 63 - d inside the tile, ascending; the others add 0
-#pragma unroll 16
-        for (int rr = 0; rr < B; ++rr) {
-          const int kk = rr + 63 - d;
-          const bool in = kk >= 0 && kk < B;
-          const float x = ahat[(in ? kk : 0) * APITCH + rr];
-          acc += in ? x : 0.0f;
-        }
+      for (int e = 0; e < 16; ++e) {
+        const int r = hf * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
+        const float a = first <= r && r < jb.nrows ? fast_exp2(s[hf][e] * SC - lse2[hf][e]) : 0.0f;
+        s[hf][e] = a;
+        sum += a;
       }
-      jb.dpart[(int64_t)t * 128 + d] = acc;
+    const float other = __shfl_xor(sum, 32);
+    const int kap = t * B + wave * 32 + c;
+    if (h == 0 && kap < jb.L_c) jb.v[kap] = sum + other;
+    if (!jb.dpart) return;
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) ahat[(wave * 32 + c) * APITCH + hf * 32 + 8 * (e >> 2) + 4 * h + (e & 3)] = s[hf][e];
+    __syncthreads();
+    // diagonals d = r - kk + 63 in [0, 127): d and d + 64 together hold one key
+    // of every row (rows up to d the first, the others the second), so a pair
+    // of lanes takes both, 32 rows each, the rows ascending
+    {
+      const int d = wave * 32 + c;
+      float lo = 0.0f, hi = 0.0f;
+#pragma unroll 16
+      for (int i = 0; i < 32; ++i) {
+        const int r = h * 32 + i;
+        const float x = ahat[((r + 63 - d) & 63) * APITCH + r];
+        lo += r <= d ? x : 0.0f;
+        hi += r <= d ? 0.0f : x;
+      }
+      const float lo2 = __shfl_xor(lo, 32), hi2 = __shfl_xor(hi, 32);
+      float* dp = jb.dpart + (int64_t)t * 128 + d;
+      if (h == 0) dp[0] = lo + lo2;
+      else dp[64] = hi2 + hi;
     }
-    __syncthreads();    // ahat and kposl are rewritten by the next tile
+    __syncthreads();    // ahat is rewritten by the next tile
   };
   fetch(0, ta);
   if (ta + 1 < tb) fetch(1, ta + 1);
