@@ -490,10 +490,20 @@ __device__ __forceinline__ void block_exscan(const int (&v)[N], int (&excl)[N], 
 }
 
 // Candidate of the smallest total union of a head (ties to the earlier one).
-__device__ __forceinline__ int best_rho(const HeadDev& hd, const int64_t* cand) {
+// The totals are read together: a chain of compared loads took most of the scan.
+__device__ __forceinline__ int best_rho(const HeadDev& hd, const int64_t* cand, int64_t* least) {
+  int64_t x[NRHO];
+#pragma unroll
+  for (int c = 0; c < NRHO; ++c) x[c] = cand[c];
+  const int alt0 = hd.rho_alt[0], alt1 = hd.rho_alt[1];
   int best = 0;
-  for (int c = 1; c < NRHO; ++c)
-    if (rho_candidate(hd, c) > 0 && cand[c] < cand[best]) best = c;
+  int64_t m = x[0];
+#pragma unroll
+  for (int c = 1; c < NRHO; ++c) {
+    const bool in = c < 4 || (c == 4 ? alt0 : alt1) > 0;
+    if (in && x[c] < m) { m = x[c]; best = c; }
+  }
+  *least = m;
   return best;
 }
 
@@ -520,9 +530,12 @@ __global__ __launch_bounds__(SCAN_T) void k_blocks_scan(const HeadDev* heads, in
   __shared__ unsigned long long sh_all;
   if (threadIdx.x == 0) sh_all = 0;
   __syncthreads();
-  for (int h = threadIdx.x; h < nheads; h += SCAN_T)
-    atomicAdd(&sh_all, (unsigned long long)cand[(int64_t)h * NRHO + best_rho(heads[h], cand + (int64_t)h * NRHO)]);
-  const int best = best_rho(hd, cand + (int64_t)blockIdx.x * NRHO);
+  int64_t least;
+  for (int h = threadIdx.x; h < nheads; h += SCAN_T) {
+    best_rho(heads[h], cand + (int64_t)h * NRHO, &least);
+    atomicAdd(&sh_all, (unsigned long long)least);
+  }
+  const int best = best_rho(hd, cand + (int64_t)blockIdx.x * NRHO, &least);
   const int rho = rho_candidate(hd, best), ngroups = groups_for(hd.nbq, R, rho);
   const int32_t* gsize = gcnt + ((int64_t)blockIdx.x * NRHO + best) * max_groups;
   __syncthreads();
@@ -819,11 +832,19 @@ __global__ __launch_bounds__(MAP_T) void k_item_map(const float* cost, int64_t n
   while (n2 < m.nruns) n2 <<= 1;
   for (int j = tid; j < n2; j += MAP_T) {
     float mx = 0.0f, s = 0.0f;
-    if (j < m.nruns)
-      for (int64_t i = (int64_t)j * m.run; i < min(n, (int64_t)(j + 1) * m.run); ++i) {
-        mx = fmaxf(mx, cost[i]);
-        s += cost[i];
+    if (j < m.nruns) {
+      const int64_t i1 = min(n, (int64_t)(j + 1) * m.run);
+      for (int64_t i = (int64_t)j * m.run; i < i1; i += 16) {
+        float x[16];                     // together: the loads are the pass's time
+#pragma unroll
+        for (int u = 0; u < 16; ++u) x[u] = i + u < i1 ? cost[i + u] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+          mx = fmaxf(mx, x[u]);
+          s += x[u];
+        }
       }
+    }
     key[j] = j < m.nruns ? ((uint64_t)__float_as_uint(mx) << 32) | (0xffffffffu - (uint32_t)j) : 0;
     sum[j] = s;
   }
