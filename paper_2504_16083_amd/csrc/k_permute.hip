@@ -71,7 +71,8 @@ hipError_t launch_permute(const void* src, int64_t ss, void* dst, int64_t ds, co
   const uint8_t* s = reinterpret_cast<const uint8_t*>(src);
   uint8_t* d = reinterpret_cast<uint8_t*>(dst);
   const int64_t vecs = row_bytes / 16;
-  if (vecs <= 256 && (vecs & (vecs - 1)) == 0 && n <= 0x7fffffff) {
+  // n is an int there, and a launch holds fewer than 2^32 threads (a quarter of the vectors)
+  if (vecs <= 256 && (vecs & (vecs - 1)) == 0 && n <= 0x7fffffff && n <= ((int64_t)1 << 33) / vecs) {
     int shift = 0;
     while ((1 << shift) < vecs) ++shift;
     const int64_t per = (int64_t)(256 >> shift) * PU;
