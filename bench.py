@@ -34,15 +34,15 @@ FLOP_PER_BLOCK = 4 * 64 * 64 * 128
 
 # HBM traffic of one k_attention launch on the 1M workload, from two rocprofv3
 # --pmc passes (FETCH_SIZE, then WRITE_SIZE, KiB per dispatch) scaled by what
-# the same counters read for a plain 1 GiB copy (read x1.939, write x1.000).
+# the same counters read for a plain 1 GiB copy (read x1.969, write x1.000).
 # Keyed by the SHA-256 prefix of the sources that decide the launch's memory
 # traffic (the kernel, the block index and work list, the runtime that orders
 # them): once any of them changes the counters are stale and `traffic` is
 # reported as null.
 TRAFFIC_SOURCES = ("k_attention.hip", "k_blocks.hip", "runtime.hip")
 TRAFFIC = {
-    "b01aa7b3395f3a7b": {"workload": "cfg4_mm_1m", "fetch_kib": 542877060, "write_kib": 7698770,
-                         "fetch_scale": 1.939, "write_scale": 1.000},
+    "e04c54b154e48e56": {"workload": "cfg4_mm_1m", "fetch_kib": 478466871, "write_kib": 8000374,
+                         "fetch_scale": 1.969, "write_scale": 1.000},
 }
 
 
