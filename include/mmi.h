@@ -227,7 +227,13 @@ int mmi_plan_create(mmi_ctx* ctx, const mmi_problem* prob, const mmi_head_cfg* c
 /* Block-sparse causal attention over the plan (Algorithms 5-7): gathers
  * permuted Q/K/V rows inside the kernel, online softmax in fp32, P rounded
  * to bf16 for the PV product, O written as bf16 (round to nearest even) in
- * original token order. lse: device float [Hq][S] natural-log LSE, or NULL. */
+ * original token order. lse: device float [Hq][S] natural-log LSE, or NULL.
+ * Executes of one plan may be enqueued on several streams: those of a plan
+ * with split rows (mmi_head_stats.split_rows), which share its partials, run
+ * one after another, the others may overlap. Replays of a graph that captured
+ * an execute are the caller's to order: after the plan's creation, before its
+ * destruction and, if it has split rows, not beside another execute or replay
+ * of the same plan. */
 int mmi_plan_execute(mmi_plan* plan, const void* q, const void* k, const void* v,
                      void* o, float* lse, void* stream);
 

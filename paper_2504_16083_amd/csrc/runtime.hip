@@ -162,7 +162,14 @@ struct HostHead {
 
 }  // namespace mmi
 
-constexpr size_t NQUEUES = 8;      // streams of one plan whose launches are persistent
+// What one execute of a plan uses alone: item counters (set `index in
+// mmi_plan::lanes` of d_queues) and, if the plan has split row groups, the
+// plan's only split partials.
+struct Lane {
+  hipStream_t stream = nullptr;    // stream of its last launch
+  hipEvent_t done = nullptr;       // after that launch (none in scratch mode: one stream, one execute)
+};
+constexpr size_t NLANES = 8;       // streams of one plan whose launches are persistent
 
 struct mmi_plan {
   mmi_ctx* ctx = nullptr;
@@ -183,14 +190,15 @@ struct mmi_plan {
   int64_t nitems = 0, nsplit = 0, nparts = 0;
   int32_t* d_item_map = nullptr;  // [8][map_len] work items per XCD
   int64_t map_len = 0;
-  int32_t* d_queues = nullptr;    // [NQUEUES][QUEUE_INTS] item counters of the attention launches
-  std::vector<hipStream_t> queue_of;  // stream that uses queue i
+  int32_t* d_queues = nullptr;    // [NLANES][QUEUE_INTS] item counters of the attention launches
+  std::vector<Lane> lanes;        // in use so far
   int R = 1;                      // query blocks per attention work item
   int32_t* d_tpos = nullptr;
   std::vector<uint8_t> mod;       // host modality of every position (all 0 without a layout)
   std::vector<float*> est_lse2;  // per rowset
   std::vector<std::vector<uint8_t>> keep;   // host sources of asynchronous uploads
-  hipEvent_t ev[7] = {};          // stage boundaries: create 0..3, execute 4..6
+  hipEvent_t ev[7] = {};          // stage boundaries: create 0..3, execute 4..6 (6: launches without a lane)
+  hipEvent_t ev_end = nullptr;    // end of the last execute: its lane's event or ev[6]
   int64_t nnz_all = 0;
   int64_t gnnz_all = 0;
   bool executed = false;
@@ -930,8 +938,8 @@ static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi
   const MapShape ms = map_shape(P->nitems);
   P->map_len = P->nitems > 0 ? (int64_t)ms.cap * ms.run : 0;
   P->d_item_map = dalloc<int32_t>(P, (size_t)8 * P->map_len);
-  P->d_queues = dalloc<int32_t>(P, (size_t)NQUEUES * QUEUE_INTS);
-  HIPCHK(launch_item_map(d_cost, P->nitems, P->d_item_map, P->d_queues, NQUEUES, st));
+  P->d_queues = dalloc<int32_t>(P, (size_t)NLANES * QUEUE_INTS);
+  HIPCHK(launch_item_map(d_cost, P->nitems, P->d_item_map, P->d_queues, (int)NLANES, st));
   mark(P, 3, st);
   P->nnz_all = nnz_all;
   P->gnnz_all = gnnz_all;
@@ -1073,26 +1081,37 @@ static void plan_check(mmi_plan* P) {
   if (!e.empty()) fail(MMI_ERR_INTERNAL, "plan check, work list: %s", e.c_str());
 }
 
-// Item counters of an execute on stream st: launches on one stream follow
-// each other, so each stream the plan runs on gets a set of its own (their
-// last launch leaves it cleared). A captured launch may be replayed beside
-// anything, the per-thread stream is a different one in every thread, and a
-// plan has NQUEUES sets: those launches take one workgroup per item (nullptr).
-static int32_t* queue_for(mmi_plan* P, hipStream_t st) {
+// The lane of an execute on stream st. Launches on one stream follow each
+// other, so without split row groups each stream the plan runs on has a lane
+// of its own, and launches on several streams may overlap. A plan with split
+// row groups has one set of partials (up to 131 KB a part), which a launch
+// writes and its merge reads: it has one lane, and each execute waits for the
+// one before. A captured launch may be replayed beside anything, the
+// per-thread stream is a different one in every thread, and a plan has NLANES
+// lanes: those launches have none (nullptr) and take one workgroup per item.
+static Lane* lane_for(mmi_plan* P, hipStream_t st) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (!P->d_queues || st == hipStreamPerThread) return nullptr;
+  if (!P->d_queues) return nullptr;
   if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
     (void)hipGetLastError();
     return nullptr;
   }
   if (cap != hipStreamCaptureStatusNone) return nullptr;
   size_t i = 0;
-  while (i < P->queue_of.size() && P->queue_of[i] != st) ++i;
-  if (i == P->queue_of.size()) {
-    if (i == NQUEUES) return nullptr;
-    P->queue_of.push_back(st);
+  if (P->nsplit == 0) {
+    if (st == hipStreamPerThread) return nullptr;
+    while (i < P->lanes.size() && P->lanes[i].stream != st) ++i;
+    if (i == NLANES) return nullptr;
   }
-  return P->d_queues + i * QUEUE_INTS;
+  if (i == P->lanes.size()) {
+    Lane l;
+    if (!P->scratch) HIPCHK(hipEventCreate(&l.done));
+    P->lanes.push_back(l);
+  }
+  Lane* l = &P->lanes[i];
+  if (l->done && P->nsplit > 0) HIPCHK(hipStreamWaitEvent(st, l->done, 0));
+  l->stream = st;
+  return l;
 }
 
 static void plan_execute_impl(mmi_plan* P, const void* q, const void* k, const void* v, void* o, float* lse,
@@ -1118,13 +1137,15 @@ static void plan_execute_impl(mmi_plan* P, const void* q, const void* k, const v
   a.map_len = P->map_len;
   a.map_run = map_shape(P->nitems).run;
   a.R = P->R;
-  a.queue = queue_for(P, st);
+  Lane* lane = lane_for(P, st);
+  a.queue = lane ? P->d_queues + (lane - P->lanes.data()) * QUEUE_INTS : nullptr;
   a.cus = P->ctx->cus;
   mark(P, 4, st);
   HIPCHK(launch_attention(a, st));
   mark(P, 5, st);
   HIPCHK(launch_combine(a, P->d_splits, P->nsplit, st));
-  mark(P, 6, st);
+  P->ev_end = lane ? lane->done : P->ev[6];
+  if (P->ev_end) HIPCHK(hipEventRecord(P->ev_end, st));
   P->stream = st;
   P->executed = true;
 }
@@ -1271,6 +1292,8 @@ int mmi_plan_destroy(mmi_plan* plan) {
     free_plan_buffers(plan);
     for (auto& e : plan->ev)
       if (e) (void)hipEventDestroy(e);
+    for (auto& l : plan->lanes)
+      if (l.done) (void)hipEventDestroy(l.done);
     --plan->ctx->live_plans;
     delete plan;
   });
@@ -1337,7 +1360,7 @@ int mmi_plan_timing_get(mmi_plan* P, mmi_plan_timing* out) {
     HIPCHK(hipEventElapsedTime(&t.index_ms, P->ev[2], P->ev[3]));
     if (P->executed) {
       HIPCHK(hipEventElapsedTime(&t.attn_ms, P->ev[4], P->ev[5]));
-      HIPCHK(hipEventElapsedTime(&t.combine_ms, P->ev[5], P->ev[6]));
+      HIPCHK(hipEventElapsedTime(&t.combine_ms, P->ev[5], P->ev_end));
     }
     t.computed_blocks = P->nnz_all;
     t.work_items = P->nitems;

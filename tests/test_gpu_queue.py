@@ -43,6 +43,34 @@ def test_streams_share_a_plan(ctx):
     plan.destroy()
 
 
+@pytest.mark.parametrize("split", [True, False])
+def test_streams_with_their_own_inputs(ctx, split):
+    """Launches of one plan in flight on several streams, each on inputs of its own: every output bitwise that of the
+    same call made alone. With split row groups they share the plan's partials."""
+    from paper_2504_16083_amd import mmi
+    print(f"[gpu] queue streams, own inputs, split={split}", flush=True)
+    S, n = (5000, 6) if split else (3000, 6)
+    mix = [C.global_head(C.dense()), C.global_head(C.ashape(64, 500)), C.global_head(C.ashape(64, 200)),
+           C.global_head(C.ashape(64, 200))]
+    heads = mix * 2 if split else [C.global_head(C.dense())] * 8
+    ins = [_layer(S, 8, 2, 20 + i) for i in range(n)]
+    plan = mmi.Plan(ctx, mmi.Problem(S, 8, 2, None), heads, *ins[0][:2])
+    assert (sum(plan.stats(h).split_rows for h in range(8)) > 0) == split
+    want = [(torch.empty_like(ins[0][0]), torch.empty(8, S, device="cuda")) for _ in ins]
+    for x, (o, lse) in zip(ins, want):
+        plan.execute(*x, o, lse)
+        torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(n)]
+    got = [(torch.full_like(ins[0][0], 7.0), torch.full((8, S), 7.0, device="cuda")) for _ in range(5 * n)]
+    torch.cuda.synchronize()
+    for i, (o, lse) in enumerate(got):
+        plan.execute(*ins[i % n], o, lse, streams[(i + i // n) % n])
+    torch.cuda.synchronize()
+    for i, (o, lse) in enumerate(got):
+        assert torch.equal(o, want[i % n][0]) and torch.equal(lse, want[i % n][1]), i
+    plan.destroy()
+
+
 def test_graph_replay(ctx):
     """A captured execute replayed between eager ones on new inputs."""
     from paper_2504_16083_amd import mmi
