@@ -168,8 +168,9 @@ struct HostHead {
 struct Lane {
   hipStream_t stream = nullptr;    // stream of its last launch
   hipEvent_t done = nullptr;       // after that launch (none in scratch mode: one stream, one execute)
+  uint64_t used = 0;               // execute that used it last
 };
-constexpr size_t NLANES = 8;       // streams of one plan whose launches are persistent
+constexpr size_t NLANES = 8;       // launches of one plan that may overlap
 
 struct mmi_plan {
   mmi_ctx* ctx = nullptr;
@@ -192,6 +193,7 @@ struct mmi_plan {
   int64_t map_len = 0;
   int32_t* d_queues = nullptr;    // [NLANES][QUEUE_INTS] item counters of the attention launches
   std::vector<Lane> lanes;        // in use so far
+  uint64_t executes = 0;
   int R = 1;                      // query blocks per attention work item
   int32_t* d_tpos = nullptr;
   std::vector<uint8_t> mod;       // host modality of every position (all 0 without a layout)
@@ -1081,14 +1083,16 @@ static void plan_check(mmi_plan* P) {
   if (!e.empty()) fail(MMI_ERR_INTERNAL, "plan check, work list: %s", e.c_str());
 }
 
-// The lane of an execute on stream st. Launches on one stream follow each
-// other, so without split row groups each stream the plan runs on has a lane
-// of its own, and launches on several streams may overlap. A plan with split
-// row groups has one set of partials (up to 131 KB a part), which a launch
-// writes and its merge reads: it has one lane, and each execute waits for the
-// one before. A captured launch may be replayed beside anything, the
-// per-thread stream is a different one in every thread, and a plan has NLANES
-// lanes: those launches have none (nullptr) and take one workgroup per item.
+// The lane of an execute on stream st. Without split row groups each stream
+// the plan runs on has a lane, and launches on several streams may overlap;
+// beyond NLANES streams (and on the per-thread stream, which is a different
+// one in every thread) a launch takes the lane used longest ago. A plan with
+// split row groups has one set of partials (up to 131 KB a part), which a
+// launch writes and its merge reads: it has one lane. The stream always waits
+// for the lane's last launch: a handle may be that of a new stream, and the
+// wait costs nothing on the stream that launch ran on. A captured launch may
+// be replayed beside anything: it has no lane (nullptr) and takes one
+// workgroup per item.
 static Lane* lane_for(mmi_plan* P, hipStream_t st) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (!P->d_queues) return nullptr;
@@ -1097,20 +1101,24 @@ static Lane* lane_for(mmi_plan* P, hipStream_t st) {
     return nullptr;
   }
   if (cap != hipStreamCaptureStatusNone) return nullptr;
+  const size_t most = P->nsplit > 0 ? 1 : NLANES;
   size_t i = 0;
-  if (P->nsplit == 0) {
-    if (st == hipStreamPerThread) return nullptr;
-    while (i < P->lanes.size() && P->lanes[i].stream != st) ++i;
-    if (i == NLANES) return nullptr;
-  }
+  while (i < P->lanes.size() && (st == hipStreamPerThread || P->lanes[i].stream != st)) ++i;
   if (i == P->lanes.size()) {
-    Lane l;
-    if (!P->scratch) HIPCHK(hipEventCreate(&l.done));
-    P->lanes.push_back(l);
+    if (i < most) {
+      Lane l;
+      if (!P->scratch) HIPCHK(hipEventCreate(&l.done));
+      P->lanes.push_back(l);
+    } else {
+      i = 0;
+      for (size_t j = 1; j < most; ++j)
+        if (P->lanes[j].used < P->lanes[i].used) i = j;
+    }
   }
   Lane* l = &P->lanes[i];
-  if (l->done && P->nsplit > 0) HIPCHK(hipStreamWaitEvent(st, l->done, 0));
+  if (l->done) HIPCHK(hipStreamWaitEvent(st, l->done, 0));
   l->stream = st;
+  l->used = ++P->executes;
   return l;
 }
 

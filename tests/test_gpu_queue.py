@@ -71,6 +71,33 @@ def test_streams_with_their_own_inputs(ctx, split):
     plan.destroy()
 
 
+def test_short_lived_streams(ctx):
+    """More streams than counter sets, each destroyed right after its launch (its handle may come back for the next
+    stream): every output bitwise that of the same call made alone."""
+    import ctypes
+    from paper_2504_16083_amd import mmi
+    print("[gpu] queue short-lived streams", flush=True)
+    hip = ctypes.CDLL("libamdhip64.so")
+    S, n = 3000, 5
+    ins = [_layer(S, 8, 2, 40 + i) for i in range(n)]
+    plan = mmi.Plan(ctx, mmi.Problem(S, 8, 2, None), [C.global_head(C.dense())] * 8, *ins[0][:2])
+    want = [torch.empty_like(ins[0][0]) for _ in ins]
+    for x, o in zip(ins, want):
+        plan.execute(*x, o)
+    got = [torch.full_like(want[0], 7.0) for _ in range(24)]
+    torch.cuda.synchronize()
+    for i, o in enumerate(got):
+        st = ctypes.c_void_p()
+        assert hip.hipStreamCreate(ctypes.byref(st)) == 0
+        plan.execute(*ins[i % n], o, None, st.value)
+        assert hip.hipStreamDestroy(st) == 0
+    torch.cuda.synchronize()
+    for i, o in enumerate(got):
+        assert torch.equal(o, want[i % n]), i
+    plan.execute(*ins[0], got[0])       # the default stream, after the last of them
+    plan.destroy()
+
+
 def test_graph_replay(ctx):
     """A captured execute replayed between eager ones on new inputs."""
     from paper_2504_16083_amd import mmi
