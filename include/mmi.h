@@ -215,7 +215,8 @@ int mmi_ctx_destroy(mmi_ctx* ctx);
 
 /* Estimation, choices, permutations and block index of every head
  * (Algorithms 1-3 up to the kernel launch). Enqueued on `stream`; the call
- * synchronises once with it (to size the block index). q, k: device
+ * synchronises once with it (to size the block index), and the rest may still
+ * run when it returns: executes on any stream wait for it. q, k: device
  * tensors described by `prob`; cfgs: host array [Hq]. Block (i, j) is
  * selected iff some query of permuted query block i and key of permuted key
  * block j satisfy k <= q in original positions and the head's predicate, or

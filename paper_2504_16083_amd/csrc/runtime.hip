@@ -799,7 +799,8 @@ static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi
   // estimation -> choices
   const Tensor tq{q, p.q_stride_s, p.q_stride_h}, tk{k, p.k_stride_s, p.k_stride_h};
   if (!P->scratch)
-    for (auto& e : P->ev) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableSystemFence));   // stage times only
+    for (int i = 0; i < 7; ++i)      // streams wait for 3; the others are for stage times only
+      HIPCHK(hipEventCreateWithFlags(&P->ev[i], i == 3 ? hipEventDefault : hipEventDisableSystemFence));
   // members of the estimation groups that read the same keys: row sets per
   // KV head, score jobs per (KV head, key map)
   auto grouped = [](int n, auto key_of, int& ngrp, int& nr) {
@@ -947,6 +948,14 @@ static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi
   P->gnnz_all = gnnz_all;
 }
 
+// Waits until the plan's creation and what runs on its stream are done (after
+// a captured execute, or one on another stream, that stream alone does not
+// cover the creation).
+static void sync_plan(mmi_plan* P) {
+  HIPCHK(hipStreamSynchronize(P->stream));
+  if (P->ev[3]) HIPCHK(hipEventSynchronize(P->ev[3]));
+}
+
 // What mmi_plan_stats takes from the device, for every head of the plan (the
 // plan's tables do not change after its creation).
 static std::vector<HeadStatDev> read_stats(mmi_plan* P) {
@@ -964,6 +973,7 @@ static std::vector<HeadStatDev> read_stats(mmi_plan* P) {
     max_nbq = std::max(max_nbq, P->heads[h].nbq);
   }
   std::vector<HeadStatDev> out(P->Hq);
+  if (P->ev[3]) HIPCHK(hipStreamWaitEvent(P->stream, P->ev[3], 0));
   uint8_t* d = static_cast<uint8_t*>(P->ctx->alloc.get(bytes));
   hipError_t e = hipMemcpyAsync(d, host.data(), bytes, hipMemcpyHostToDevice, P->stream);
   if (e == hipSuccess)
@@ -1006,7 +1016,7 @@ static void make_columns(mmi_plan* P) {
 // block index and row-group unions, then the work list and item map.
 static void plan_check(mmi_plan* P) {
   HIPCHK(hipSetDevice(P->ctx->device));
-  HIPCHK(hipStreamSynchronize(P->stream));
+  sync_plan(P);
   make_columns(P);
   auto get = [](const int32_t* src, size_t n) {
     std::vector<int32_t> v(std::max<size_t>(n, 1));
@@ -1116,7 +1126,9 @@ static Lane* lane_for(mmi_plan* P, hipStream_t st) {
     }
   }
   Lane* l = &P->lanes[i];
-  if (l->done) HIPCHK(hipStreamWaitEvent(st, l->done, 0));
+  // a lane's first launch waits for the end of the creation, which may still
+  // be filling the work list and clearing the counters on its own stream
+  if (l->done) HIPCHK(hipStreamWaitEvent(st, l->used ? l->done : P->ev[3], 0));
   l->stream = st;
   l->used = ++P->executes;
   return l;
@@ -1341,7 +1353,7 @@ int mmi_plan_pair_counts(mmi_plan* P, int head, int64_t* useful, int64_t* comput
     if (!P || !useful || !computed) fail(MMI_ERR_INVALID_ARG, "plan/useful/computed is NULL");
     if (head < 0 || head >= P->Hq) fail(MMI_ERR_INVALID_ARG, "head %d out of range", head);
     HIPCHK(hipSetDevice(P->ctx->device));
-    HIPCHK(hipStreamSynchronize(P->stream));
+    sync_plan(P);
     int32_t gp[2];
     HIPCHK(hipMemcpy(gp, P->heads[head].gp, sizeof gp, hipMemcpyDeviceToHost));
     void* d = P->ctx->alloc.get(sizeof(unsigned long long));
@@ -1361,7 +1373,7 @@ int mmi_plan_timing_get(mmi_plan* P, mmi_plan_timing* out) {
   return guarded([&] {
     if (!P || !out) fail(MMI_ERR_INVALID_ARG, "plan/out is NULL");
     HIPCHK(hipSetDevice(P->ctx->device));
-    HIPCHK(hipStreamSynchronize(P->stream));
+    sync_plan(P);
     mmi_plan_timing t{};
     HIPCHK(hipEventElapsedTime(&t.est_ms, P->ev[0], P->ev[1]));
     HIPCHK(hipEventElapsedTime(&t.select_ms, P->ev[1], P->ev[2]));
@@ -1383,7 +1395,7 @@ int mmi_plan_export(mmi_plan* P, int head, int what, int slot, void* dst, size_t
     if (!P) fail(MMI_ERR_STATE, "plan is NULL");
     if (head < 0 || head >= P->Hq) fail(MMI_ERR_INVALID_ARG, "head %d out of range", head);
     HIPCHK(hipSetDevice(P->ctx->device));
-    HIPCHK(hipStreamSynchronize(P->stream));
+    sync_plan(P);
     const HostHead& H = P->hh[head];
     const HeadDev& hd = P->heads[head];
     const void* src = nullptr;

@@ -71,6 +71,36 @@ def test_streams_with_their_own_inputs(ctx, split):
     plan.destroy()
 
 
+@pytest.mark.parametrize("S", [300, 5000])
+def test_created_on_one_stream_executed_on_others(ctx, S):
+    """Nothing but the library orders the executes behind the creation's last launches (work list, item map, cleared
+    counters); the buffers come from earlier plans, so what they hold before is another plan's. Statistics and exports
+    likewise."""
+    from paper_2504_16083_amd import mmi
+    print(f"[gpu] queue creation S={S}", flush=True)
+    heads = [C.global_head(C.dense()), C.global_head(C.grid(20, 30)), C.global_head(C.ashape(64, 500)),
+             C.global_head(C.vslash(100, 50))] * 2
+    q, k, v = _layer(S, 8, 2, 5)
+    prob = mmi.Problem(S, 8, 2, None)
+    want = torch.empty_like(q)
+    mmi.mmi_attention(ctx, prob, heads, q, k, v, want)
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    for i in range(6):
+        other = mmi.Plan(ctx, mmi.Problem(S - i, 8, 2, None), heads[::-1], q, k)    # leaves its tables in the buffers
+        other.destroy()
+        outs = [torch.full_like(q, 7.0) for _ in streams]
+        torch.cuda.synchronize()
+        plan = mmi.Plan(ctx, prob, heads, q, k, streams[i % 4])
+        for st, o in zip(streams, outs):
+            plan.execute(q, k, v, o, None, st)
+        nnz = [plan.stats(h).nnz_blocks for h in range(8)]
+        assert nnz == [len(plan.export(h, "col_idx")) for h in range(8)]
+        torch.cuda.synchronize()
+        for j, o in enumerate(outs):
+            assert torch.equal(o, want), (i, j)
+        plan.destroy()
+
+
 def test_short_lived_streams(ctx):
     """More streams than counter sets, each destroyed right after its launch (its handle may come back for the next
     stream): every output bitwise that of the same call made alone."""
