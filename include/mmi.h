@@ -258,6 +258,8 @@ int mmi_plan_pair_counts(mmi_plan* plan, int head, int64_t* useful, int64_t* com
 /* Stage durations (synchronises with the plan's stream). */
 int mmi_plan_timing_get(mmi_plan* plan, mmi_plan_timing* out);
 
+/* Waits for the plan's executes on every stream (replays of a captured one
+ * are the caller's to wait for), then gives its buffers back. */
 int mmi_plan_destroy(mmi_plan* plan);
 
 /* create + execute + destroy. */

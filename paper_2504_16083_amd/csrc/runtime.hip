@@ -1160,13 +1160,14 @@ static void plan_execute_impl(mmi_plan* P, const void* q, const void* k, const v
   Lane* lane = lane_for(P, st);
   a.queue = lane ? P->d_queues + (lane - P->lanes.data()) * QUEUE_INTS : nullptr;
   a.cus = P->ctx->cus;
-  mark(P, 4, st);
-  HIPCHK(launch_attention(a, st));
-  mark(P, 5, st);
-  HIPCHK(launch_combine(a, P->d_splits, P->nsplit, st));
-  P->ev_end = lane ? lane->done : P->ev[6];
-  if (P->ev_end) HIPCHK(hipEventRecord(P->ev_end, st));
   P->stream = st;
+  mark(P, 4, st);
+  hipError_t e = launch_attention(a, st);
+  mark(P, 5, st);
+  if (e == hipSuccess) e = launch_combine(a, P->d_splits, P->nsplit, st);
+  P->ev_end = lane ? lane->done : P->ev[6];      // recorded also behind a launch whose merge failed
+  if (P->ev_end) HIPCHK(hipEventRecord(P->ev_end, st));
+  HIPCHK(e);
   P->executed = true;
 }
 
@@ -1308,7 +1309,10 @@ int mmi_plan_destroy(mmi_plan* plan) {
   return guarded([&] {
     if (!plan) fail(MMI_ERR_INVALID_ARG, "plan is NULL");
     (void)hipSetDevice(plan->ctx->device);
-    HIPCHK(hipStreamSynchronize(plan->stream));
+    // the buffers go to the next plan: every launch that reads them is over
+    sync_plan(plan);
+    for (auto& l : plan->lanes)
+      if (l.done) HIPCHK(hipEventSynchronize(l.done));
     free_plan_buffers(plan);
     for (auto& e : plan->ev)
       if (e) (void)hipEventDestroy(e);

@@ -101,6 +101,34 @@ def test_created_on_one_stream_executed_on_others(ctx, S):
         plan.destroy()
 
 
+def test_destroyed_while_streams_still_execute(ctx):
+    """Destroying a plan waits for its launches on every stream; the next plan takes over its buffers at once."""
+    from paper_2504_16083_amd import mmi
+    print("[gpu] queue destroy", flush=True)
+    S = 3000
+    q, k, v = _layer(S, 8, 2, 6)
+    prob, dense = mmi.Problem(S, 8, 2, None), [C.global_head(C.dense())] * 8
+    want, want2 = torch.empty_like(q), torch.empty_like(q)
+    mmi.mmi_attention(ctx, prob, dense, q, k, v, want)
+    mmi.mmi_attention(ctx, prob, [C.global_head(C.ashape(64, 300))] * 8, q, k, v, want2)
+    streams = [torch.cuda.Stream() for _ in range(6)]
+    for r in range(3):
+        outs, o2, last = [torch.full_like(q, 7.0) for _ in range(24)], torch.full_like(q, 7.0), torch.empty_like(q)
+        torch.cuda.synchronize()
+        plan = mmi.Plan(ctx, prob, dense, q, k)
+        for i, o in enumerate(outs):
+            plan.execute(q, k, v, o, None, streams[i % 6])
+        plan.execute(q, k, v, last, None, streams[r])
+        plan.destroy()
+        nxt = mmi.Plan(ctx, prob, [C.global_head(C.ashape(64, 300))] * 8, q, k)
+        nxt.execute(q, k, v, o2)
+        torch.cuda.synchronize()
+        for i, o in enumerate(outs):
+            assert torch.equal(o, want), (r, i)
+        assert torch.equal(o2, want2), r
+        nxt.destroy()
+
+
 def test_short_lived_streams(ctx):
     """More streams than counter sets, each destroyed right after its launch (its handle may come back for the next
     stream): every output bitwise that of the same call made alone."""
