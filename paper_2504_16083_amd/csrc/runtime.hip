@@ -167,10 +167,12 @@ struct HostHead {
 // plan's only split partials.
 struct Lane {
   hipStream_t stream = nullptr;    // stream of its last launch
-  hipEvent_t done = nullptr;       // after that launch (none in scratch mode: one stream, one execute)
+  hipEvent_t done = nullptr;       // after that launch (none in a one-shot plan: one stream, one execute)
   uint64_t used = 0;               // execute that used it last
 };
 constexpr size_t NLANES = 8;       // launches of one plan that may overlap
+// Events that other streams of the same device wait for.
+constexpr unsigned ORDER_EVENT = hipEventReleaseToDevice;
 
 struct mmi_plan {
   mmi_ctx* ctx = nullptr;
@@ -199,8 +201,10 @@ struct mmi_plan {
   std::vector<uint8_t> mod;       // host modality of every position (all 0 without a layout)
   std::vector<float*> est_lse2;  // per rowset
   std::vector<std::vector<uint8_t>> keep;   // host sources of asynchronous uploads
-  hipEvent_t ev[7] = {};          // stage boundaries: create 0..3, execute 4..6 (6: launches without a lane)
-  hipEvent_t ev_end = nullptr;    // end of the last execute: its lane's event or ev[6]
+  hipEvent_t ev[7] = {};          // stage boundaries: create 0..3, execute 4..6 (6: captured ones)
+  hipEvent_t ev_end = nullptr;    // end of the last execute with a lane
+  bool captured = false;          // the last execute was captured
+  bool one_shot = false;          // created, executed and destroyed on one stream inside one call
   int64_t nnz_all = 0;
   int64_t gnnz_all = 0;
   bool executed = false;
@@ -800,7 +804,7 @@ static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi
   const Tensor tq{q, p.q_stride_s, p.q_stride_h}, tk{k, p.k_stride_s, p.k_stride_h};
   if (!P->scratch)
     for (int i = 0; i < 7; ++i)      // streams wait for 3; the others are for stage times only
-      HIPCHK(hipEventCreateWithFlags(&P->ev[i], i == 3 ? hipEventDefault : hipEventDisableSystemFence));
+      HIPCHK(hipEventCreateWithFlags(&P->ev[i], i == 3 && !P->one_shot ? ORDER_EVENT : hipEventDisableSystemFence));
   // members of the estimation groups that read the same keys: row sets per
   // KV head, score jobs per (KV head, key map)
   auto grouped = [](int n, auto key_of, int& ngrp, int& nr) {
@@ -953,7 +957,7 @@ static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi
 // cover the creation).
 static void sync_plan(mmi_plan* P) {
   HIPCHK(hipStreamSynchronize(P->stream));
-  if (P->ev[3]) HIPCHK(hipEventSynchronize(P->ev[3]));
+  if (P->ev[3] && !P->one_shot) HIPCHK(hipEventSynchronize(P->ev[3]));
 }
 
 // What mmi_plan_stats takes from the device, for every head of the plan (the
@@ -1117,7 +1121,7 @@ static Lane* lane_for(mmi_plan* P, hipStream_t st) {
   if (i == P->lanes.size()) {
     if (i < most) {
       Lane l;
-      if (!P->scratch) HIPCHK(hipEventCreate(&l.done));
+      if (!P->one_shot) HIPCHK(hipEventCreateWithFlags(&l.done, ORDER_EVENT));
       P->lanes.push_back(l);
     } else {
       i = 0;
@@ -1165,8 +1169,9 @@ static void plan_execute_impl(mmi_plan* P, const void* q, const void* k, const v
   hipError_t e = launch_attention(a, st);
   mark(P, 5, st);
   if (e == hipSuccess) e = launch_combine(a, P->d_splits, P->nsplit, st);
-  P->ev_end = lane ? lane->done : P->ev[6];      // recorded also behind a launch whose merge failed
-  if (P->ev_end) HIPCHK(hipEventRecord(P->ev_end, st));
+  P->captured = !lane;
+  if (lane && lane->done) HIPCHK(hipEventRecord(P->ev_end = lane->done, st));   // also behind a launch whose merge failed
+  else mark(P, 6, st);
   HIPCHK(e);
   P->executed = true;
 }
@@ -1258,15 +1263,17 @@ int mmi_ctx_destroy(mmi_ctx* ctx) {
   });
 }
 
-// Plan creation shared by mmi_plan_create (scratch_base NULL: buffers from the
-// context's allocator) and mmi_attention_noalloc (buffers in the scratch).
+// Plan creation shared by mmi_plan_create, mmi_attention (one_shot) and
+// mmi_attention_noalloc (one_shot, buffers in the scratch instead of from the
+// context's allocator).
 static int create_plan(mmi_ctx* ctx, const mmi_problem* prob, const mmi_head_cfg* cfgs, const void* q,
-                       const void* k, void* stream, uint8_t* scratch_base, mmi_plan** out) {
+                       const void* k, void* stream, bool one_shot, uint8_t* scratch_base, mmi_plan** out) {
   mmi_plan* P = nullptr;
   int rc = guarded([&] {
     validate_inputs(prob, cfgs, q, k);     // host-only checks first
     if (!ctx || !out) fail(MMI_ERR_INVALID_ARG, "ctx/out is NULL");
     P = new mmi_plan();
+    P->one_shot = one_shot;
     P->scratch = scratch_base;
     plan_create_impl(ctx, prob, cfgs, q, k, (hipStream_t)stream, P);
     if (ctx->debug) plan_check(P);
@@ -1290,7 +1297,7 @@ static int create_plan(mmi_ctx* ctx, const mmi_problem* prob, const mmi_head_cfg
 
 int mmi_plan_create(mmi_ctx* ctx, const mmi_problem* prob, const mmi_head_cfg* cfgs, const void* q,
                     const void* k, void* stream, mmi_plan** out) {
-  return create_plan(ctx, prob, cfgs, q, k, stream, nullptr, out);
+  return create_plan(ctx, prob, cfgs, q, k, stream, false, nullptr, out);
 }
 
 int mmi_plan_execute(mmi_plan* plan, const void* q, const void* k, const void* v, void* o, float* lse,
@@ -1384,7 +1391,11 @@ int mmi_plan_timing_get(mmi_plan* P, mmi_plan_timing* out) {
     HIPCHK(hipEventElapsedTime(&t.index_ms, P->ev[2], P->ev[3]));
     if (P->executed) {
       HIPCHK(hipEventElapsedTime(&t.attn_ms, P->ev[4], P->ev[5]));
-      HIPCHK(hipEventElapsedTime(&t.combine_ms, P->ev[5], P->ev_end));
+      // the replays of a captured execute record the stage events
+      if (!P->captured || hipEventElapsedTime(&t.combine_ms, P->ev[5], P->ev[6]) != hipSuccess) {
+        (void)hipGetLastError();
+        HIPCHK(hipEventElapsedTime(&t.combine_ms, P->ev[5], P->ev_end ? P->ev_end : P->ev[6]));
+      }
     }
     t.computed_blocks = P->nnz_all;
     t.work_items = P->nitems;
@@ -1473,7 +1484,7 @@ int mmi_plan_export(mmi_plan* P, int head, int what, int slot, void* dst, size_t
 int mmi_attention(mmi_ctx* ctx, const mmi_problem* prob, const mmi_head_cfg* cfgs, const void* q, const void* k,
                   const void* v, void* o, float* lse, void* stream) {
   mmi_plan* P = nullptr;
-  int rc = mmi_plan_create(ctx, prob, cfgs, q, k, stream, &P);
+  int rc = create_plan(ctx, prob, cfgs, q, k, stream, true, nullptr, &P);
   if (rc != MMI_OK) return rc;
   rc = mmi_plan_execute(P, q, k, v, o, lse, stream);
   const int rc2 = mmi_plan_destroy(P);
@@ -1493,7 +1504,7 @@ int mmi_attention_noalloc(mmi_ctx* ctx, const mmi_problem* prob, const mmi_head_
   // one call at a time per device: the scratch holds one plan
   std::lock_guard<std::mutex> lk(g_scratch_call_mu[ctx->device]);
   mmi_plan* P = nullptr;
-  int rc = create_plan(ctx, prob, cfgs, q, k, stream, g_scratch_ptr[ctx->device], &P);
+  int rc = create_plan(ctx, prob, cfgs, q, k, stream, true, g_scratch_ptr[ctx->device], &P);
   if (rc != MMI_OK) return rc;
   rc = mmi_plan_execute(P, q, k, v, o, lse, stream);
   const int rc2 = mmi_plan_destroy(P);      // waits for the stream: the scratch is free again

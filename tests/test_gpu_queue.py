@@ -178,6 +178,28 @@ def test_graph_replay(ctx):
     plan.destroy()
 
 
+def test_stage_times_after_a_captured_execute(ctx):
+    """The stage times stay readable once an execute was captured, before and after its replay."""
+    from paper_2504_16083_amd import mmi
+    print("[gpu] queue capture, stage times", flush=True)
+    q, k, v = _layer(3000, 4, 2, 7)
+    plan = mmi.Plan(ctx, mmi.Problem(3000, 4, 2, None), [C.global_head(C.ashape(64, 300))] * 4, q, k)
+    o = torch.empty_like(q)
+    plan.execute(q, k, v, o)
+    g = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(g):
+        plan.execute(q, k, v, o)
+    assert plan.timing()["attn_ms"] > 0
+    g.replay()
+    torch.cuda.synchronize()
+    assert plan.timing()["attn_ms"] > 0
+    plan.execute(q, k, v, o)
+    t = plan.timing()
+    assert t["attn_ms"] > 0 and t["combine_ms"] >= 0
+    plan.destroy()
+
+
 @pytest.mark.parametrize("S,Hq", [(1, 1), (64, 1), (257, 1), (300, 9), (2048, 40)])
 def test_item_counts(ctx, S, Hq):
     """From one item to more than the CUs: rows all written, the plan's tables consistent."""
