@@ -214,6 +214,18 @@ inline MapShape map_shape(int64_t n) {
   const int64_t nruns = (n + run - 1) / run, avg = (nruns + 7) / 8;
   return {(int32_t)run, (int32_t)nruns, (int32_t)(avg + (avg / 4 > 1 ? avg / 4 : 1))};
 }
+// Entries of an XCD's list that start side by side: a run, or all (nobody
+// waits) where a run would leave more than an eighth of the XCD's workgroups
+// asleep, as it does in layers of under 1800 items (one head of 256K to 450K
+// tokens). Dense, one head, attention with a run waiting | nobody waiting:
+// 256K (run 16) 18.6 | 16.7 ms, 300K (18) 25.6 | 23.3, 350K (21) 33.9 | 31.5,
+// 400K (24) 42.9 | 41.1, 450K (27) 52.9 | 51.5, 500K (30) 62.7 | 63.5, 512K
+// (32) 65.1 | 67.5. (As many whole runs as give each workgroup an item, 256K
+// to 450K: 17.2, 23.1, 32.8, 41.6, 52.1.)
+inline int32_t side_by_side(int32_t run, int32_t cus) { return run < cus * 7 / 64 ? INT_BIG : run; }
+// Entries of the list that are finished before entry k starts, if it waits.
+constexpr int LEAD_SLACK = 2;            // items of the run before that may still be running
+__host__ __device__ inline int lead_need(int k, int side) { return k / side * side - LEAD_SLACK; }
 hipError_t launch_work_fill(const HeadDev* heads, int nheads, int R, const int64_t* item_base,
                             const int64_t* part_base, const int64_t* split_base, int max_groups,
                             WorkItem* items, float* cost, SplitRow* splits, hipStream_t st);
@@ -230,7 +242,7 @@ struct AttnArgs {
   int64_t nitems;
   const int32_t* item_map;    // [8][map_len]: work items of each XCD in order, -1 = none
   int64_t map_len;
-  int32_t map_run;            // consecutive entries of a list that are neighbouring items
+  int32_t side;               // entries of a list that start side by side
   float* part_o;              // [nparts][R*64][128], each row normalised by its bf16-P sum
   float* part_ml;             // [nparts][R*64][4]: running max m, bf16-P sum lo, fp32-P sum l, unused
   int32_t R;                  // query blocks per row group (1, 2 or 4)

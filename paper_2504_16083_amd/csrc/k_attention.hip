@@ -49,7 +49,6 @@ constexpr int KPITCH = 136;   // bf16 per K row in LDS (272 B): conflict-free 16
 constexpr int VPITCH = 160;   // bf16 per V row in LDS (320 B): transpose reads of 4 rows hit distinct banks
 constexpr int NSTAGE = 4;
 constexpr float RESCALE_SLACK = 8.0f;
-constexpr int LEAD_SLACK = 2;            // items of the run before that may still be running
 constexpr int LEAD_TICKS = 30;           // longest wait per union entry of the item, 10 ns ticks
 
 struct __align__(16) Stage {
@@ -556,7 +555,7 @@ __device__ __forceinline__ int take_item(const AttnArgs& a, int home, int* from)
       // whatever the other workgroups do.
       const int lead = load_item(a, it).lead;
       if (lead > 0) {
-        const int need = k / a.map_run * a.map_run - LEAD_SLACK;
+        const int need = lead_need(k, a.side);
         const uint64_t budget = (uint64_t)lead * LEAD_TICKS, t0 = __builtin_readsteadycounter();
         while (__hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < need &&
                __builtin_readsteadycounter() - t0 < budget)

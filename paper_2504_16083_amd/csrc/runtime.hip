@@ -1159,7 +1159,7 @@ static void plan_execute_impl(mmi_plan* P, const void* q, const void* k, const v
   a.part_ml = P->d_part_ml;
   a.item_map = P->d_item_map;
   a.map_len = P->map_len;
-  a.map_run = map_shape(P->nitems).run;
+  a.side = side_by_side(map_shape(P->nitems).run, P->ctx->cus);
   a.R = P->R;
   Lane* lane = lane_for(P, st);
   a.queue = lane ? P->d_queues + (lane - P->lanes.data()) * QUEUE_INTS : nullptr;
