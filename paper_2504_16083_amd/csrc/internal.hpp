@@ -214,6 +214,34 @@ inline MapShape map_shape(int64_t n) {
   const int64_t nruns = (n + run - 1) / run, avg = (nruns + 7) / 8;
   return {(int32_t)run, (int32_t)nruns, (int32_t)(avg + (avg / 4 > 1 ? avg / 4 : 1))};
 }
+// Items whose workgroups start side by side (WorkItem::lead): long walks over
+// the K and V of a head with many keys (32 KB per 64 of them, once: the key
+// layouts of a Q-Boundary head hold the same keys), which miss the 256 MB
+// last-level cache when they are read apart. Attention without | with waiting,
+// 28/4 heads unless said:
+//   from RUN_KEYS key blocks (as much as the cache), walks of RUN_STEPS steps:
+//     mixed heads 512K 303 | 283 ms, 768K 505 | 459, 1M 655 | 588;
+//   from RUN_KEYS_LONG, walks of RUN_STEPS_LONG steps, which lose each other
+//     over fewer keys: two mixed layers, 384K 202.2 | 200.3 and 251.4 | 245.1,
+//     340K 174.7 | 172.0 and 219.2 | 213.1, 300K 144.8 | 145.7 and 181.1 |
+//     178.9; below it the waiting loses: 256K 112.2 | 115.8 and 138.6 | 142.1;
+//   from RUN_KEYS_DENSE, such walks over unions that every member of the row
+//     group selects (all but the blocks past a member's last query), so that
+//     the walks of a run read the same blocks: dense 256K 489 | 453. (With
+//     three of four members as the line some walks of the mixed 256K layers
+//     wait and some do not: 115.9 and 142.9.)
+constexpr int RUN_KEYS = 8192, RUN_STEPS = 256;
+constexpr int RUN_KEYS_LONG = 4608, RUN_STEPS_LONG = 1024;
+constexpr int RUN_KEYS_DENSE = 4096;
+// WorkItem::lead of an item of `steps` of the `staged` union entries of a row
+// group of R members that computes `computed` blocks over them.
+__host__ __device__ inline int lead_steps(int S, int R, int steps, int staged, int computed) {
+  const int keys = (S + B - 1) / B;
+  const bool dense = 40 * (int64_t)computed >= 39 * (int64_t)R * staged;
+  const bool side = keys >= RUN_KEYS ? steps >= RUN_STEPS
+                                     : steps >= RUN_STEPS_LONG && keys >= (dense ? RUN_KEYS_DENSE : RUN_KEYS_LONG);
+  return side ? steps : 0;
+}
 // Entries of an XCD's list that start side by side: a run, or all (nobody
 // waits) where a run would leave more than an eighth of the XCD's workgroups
 // asleep, as it does in layers of under 1800 items (one head of 256K to 450K

@@ -751,18 +751,6 @@ hipError_t launch_group_fill(const HeadDev* heads, int nheads, int R, int max_gr
 // staged blocks, 1.75 ms per million computed blocks).
 constexpr float COST_STAGE = 1.5f, COST_COMPUTE = 1.0f;
 
-// Items whose workgroups start side by side (WorkItem::lead): those of heads
-// with at least RUN_KEYS key blocks, whose K and V (32 KB a block) outgrow the
-// 256 MB last-level cache, so that reading them apart costs HBM reads, and
-// with walks long enough to lose each other. 1M layer: attention 588 ms with
-// it, 655 without (the same workgroups free-running); 128K and 256K layers,
-// whose K/V fit the cache, lose 1-2% to the waiting.
-// Walks of RUN_STEPS_LONG steps lose each other also over half as many keys:
-// dense 256K, 32/8 heads 563 -> 514 ms, 28/4 heads 483 -> 449 (one workgroup
-// per item 530 and 463).
-constexpr int RUN_KEYS = 8192, RUN_STEPS = 256;
-constexpr int RUN_KEYS_LONG = 4096, RUN_STEPS_LONG = 1024;
-
 // Work items of every row group: nparts equal ranges of its union, with their
 // modelled cost (an item takes its share of the group's computed blocks).
 __global__ __launch_bounds__(256) void k_work_fill(const HeadDev* heads, int R, const int64_t* item_base,
@@ -793,7 +781,7 @@ __global__ __launch_bounds__(256) void k_work_fill(const HeadDev* heads, int R, 
     w.e1 = min(r0 + (c + 1) * len, r1);
     w.part = split ? (int)(pb + c) : -1;
     const int steps = w.e1 - w.e0;
-    w.lead = (hd.nbk >= RUN_KEYS && steps >= RUN_STEPS) || (hd.nbk >= RUN_KEYS_LONG && steps >= RUN_STEPS_LONG) ? steps : 0;
+    w.lead = lead_steps(hd.S, R, steps, r1 - r0, computed);
     w.pad[0] = w.pad[1] = 0;
     items[ib + c] = w;
     cost[ib + c] = per * (float)(w.e1 - w.e0);

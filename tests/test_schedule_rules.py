@@ -43,3 +43,16 @@ def test_few_workgroups_wait_for_their_first_item(run, cus):
     for n, r, wait, after in rows:
         assert wait <= wgs / 8, n
         assert after == (r - 2 if r * 8 >= wgs * 7 else -2), n
+
+
+@pytest.mark.parametrize("S,R,steps,staged,computed,lead", [
+    (1 << 19, 4, 256, 4000, 4000, True), (1 << 19, 4, 255, 4000, 16000, False),            # 8192 key blocks, any union
+    ((1 << 19) - 64, 4, 1023, 4000, 16000, False), ((1 << 19) - 64, 4, 1024, 4000, 4000, True),
+    (294912, 4, 1024, 4000, 4000, True), (294912 - 64, 4, 1024, 4000, 4000, False),        # 4608
+    (294912 - 64, 4, 1024, 4000, 15600, True), (294912 - 64, 4, 1024, 4000, 15599, False),  # every member selects it
+    (294912 - 64, 1, 1024, 4000, 4000, True), (294912 - 64, 2, 1024, 4000, 4000, False),
+    (1 << 18, 4, 1024, 1024, 4090, True), ((1 << 18) - 64, 4, 1024, 4000, 16000, False),   # 4096
+    ((1 << 18) - 63, 4, 1024, 4000, 16000, True), (4096, 4, 64, 64, 256, False)])
+def test_items_that_start_side_by_side(run, S, R, steps, staged, computed, lead):
+    """The rule counts a head's keys once, whatever its key layouts, and long walks of fewer keys."""
+    assert run(f"out(lead_steps({S}, {R}, {steps}, {staged}, {computed}));") == [[steps if lead else 0]]
