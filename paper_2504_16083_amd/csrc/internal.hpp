@@ -197,9 +197,6 @@ constexpr int NTOT = 5;
 hipError_t launch_blocks_scan(const HeadDev* heads, int nheads, int R, const int64_t* cand, const int32_t* gcnt,
                               int max_groups, int min_chunk, int items, int all_groups, int64_t* totals, hipStream_t st);
 hipError_t launch_group_fill(const HeadDev* heads, int nheads, int R, int max_groups, int max_nbk, hipStream_t st);
-// the column lists of every head: head h's at col + col_off[h]
-hipError_t launch_blocks_fill(const HeadDev* heads, int nheads, int max_nbq, const int64_t* col_off, int32_t* col,
-                              hipStream_t st);
 // Runs of consecutive work items and their slots in the item map ([8][cap *
 // run], -1 = none): 32 items per run, fewer for small layers so that every XCD
 // gets some, more where there would be over MAP_RUNS runs; at most a quarter

@@ -18,7 +18,6 @@
 //   (the attention kernel loads each key block once for all R query blocks).
 // k_blocks_scan: per head, the row-group stride, prefix sums of counts (CSR
 //   row pointers), of the group unions and of work-item counts.
-// k_blocks_fill: ascending column lists from the bitmaps.
 // k_work_fill: work items (a row group and a range of its union entries each)
 //   and the split-group table for the combine kernel.
 // k_item_map: the work items of each XCD, in order.
@@ -611,40 +610,6 @@ __device__ __forceinline__ int block_exclusive_scan(int cnt, int* wtot, int* tot
   return pre + s - cnt;
 }
 
-// Ascending column list of one query block from its bitmap (each thread's
-// words read once, kept in registers for the write): col + col_off[head] +
-// rowptr. The attention reads row-group unions; only an export or a check of
-// the index asks for these lists, so a plan makes them then (they took 200 us
-// of a 128K layer's index, 1.1 ms at 1M).
-__global__ __launch_bounds__(256) void k_blocks_fill(const HeadDev* heads, const int64_t* col_off, int32_t* col) {
-  const HeadDev hd = heads[blockIdx.x];
-  const int qb = blockIdx.y;
-  if (qb >= hd.nbq) return;
-  __shared__ int wtot[4];
-  const uint32_t* gbm = hd.bitmap + (int64_t)qb * hd.nwords;
-  const int per = (hd.nwords + 255) / 256;
-  const int w0 = threadIdx.x * per;
-  uint32_t x[GF_WORDS];
-  int cnt = 0;
-#pragma unroll
-  for (int k = 0; k < GF_WORDS; ++k) {
-    x[k] = k < per && w0 + k < hd.nwords ? gbm[w0 + k] : 0u;
-    cnt += __popc(x[k]);
-  }
-  int total;
-  int32_t* out = col + col_off[blockIdx.x];
-  int pos = hd.rowptr[qb] + block_exclusive_scan<256>(cnt, wtot, &total);
-#pragma unroll
-  for (int k = 0; k < GF_WORDS; ++k) {
-    uint32_t v = x[k];
-    while (v) {
-      const int b = __ffs(v) - 1;
-      out[pos++] = (w0 + k) * 32 + b;
-      v &= v - 1;
-    }
-  }
-}
-
 // Union entries of a row group: first the key blocks every member selects,
 // then the others, each part ascending (row groups running side by side then
 // start on the blocks they most likely share, which measured ~2% faster than
@@ -728,13 +693,6 @@ __global__ __launch_bounds__(NT) void k_group_fill(const HeadDev* heads, int R) 
       u &= u - 1;
     }
   }
-}
-
-hipError_t launch_blocks_fill(const HeadDev* heads, int nheads, int max_nbq, const int64_t* col_off, int32_t* col,
-                              hipStream_t st) {
-  if (nheads <= 0 || max_nbq <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_blocks_fill, dim3(nheads, max_nbq), dim3(256), 0, st, heads, col_off, col);
-  return hipGetLastError();
 }
 
 hipError_t launch_group_fill(const HeadDev* heads, int nheads, int R, int max_groups, int max_nbk, hipStream_t st) {

@@ -209,7 +209,6 @@ struct mmi_plan {
   int64_t gnnz_all = 0;
   bool executed = false;
   std::vector<int> rowset_n;
-  std::vector<int32_t*> col;      // column lists of the heads, once asked for
   std::vector<mmi::HeadStatDev> stats;   // of every head, filled by the first mmi_plan_stats
   int64_t device_bytes = 0;       // device memory the plan holds
   uint8_t* scratch = nullptr;     // non-null: buffers come from the no-allocation scratch
@@ -992,28 +991,22 @@ static std::vector<HeadStatDev> read_stats(mmi_plan* P) {
   return out;
 }
 
-// Column lists of every head, made when first asked for (exports, checks):
-// head h's start at plan->col[h].
-static void make_columns(mmi_plan* P) {
-  if (!P->col.empty()) return;
-  std::vector<int64_t> off(P->Hq);
+// Column list of a head (ascending key blocks of each query block; H.nnz of
+// them), from its bitmap: only exports and checks ask for it, and the host
+// makes it, so that asking needs no device memory.
+static void column_list(const mmi_plan* P, int head, int32_t* out) {
+  const HeadDev& hd = P->heads[head];
+  std::vector<uint32_t> bits((size_t)hd.nbq * hd.nwords);
+  HIPCHK(hipMemcpy(bits.data(), hd.bitmap, bits.size() * sizeof(uint32_t), hipMemcpyDeviceToHost));
   int64_t n = 0;
-  int max_nbq = 0;
-  for (int h = 0; h < P->Hq; ++h) {
-    off[h] = n;
-    n += P->hh[h].nnz;
-    max_nbq = std::max(max_nbq, P->heads[h].nbq);
-  }
-  int64_t* d_off = nullptr;
-  {
-    Pack pk;
-    pk.add(off, d_off);
-    send(P, pk);
-  }
-  int32_t* col = dalloc<int32_t>(P, n);
-  HIPCHK(launch_blocks_fill(P->d_heads, P->Hq, max_nbq, d_off, col, P->stream));
-  HIPCHK(hipStreamSynchronize(P->stream));
-  for (int h = 0; h < P->Hq; ++h) P->col.push_back(col + off[h]);
+  for (uint32_t v : bits) n += __builtin_popcount(v);
+  if (n != P->hh[head].nnz)
+    fail(MMI_ERR_INTERNAL, "head %d: %lld selected blocks in its bitmap, the plan counted %lld", head, (long long)n,
+         (long long)P->hh[head].nnz);
+  const uint32_t* row = bits.data();
+  for (int qb = 0; qb < hd.nbq; ++qb, row += hd.nwords)
+    for (int w = 0; w < hd.nwords; ++w)
+      for (uint32_t v = row[w]; v; v &= v - 1) *out++ = w * 32 + __builtin_ctz(v);
 }
 
 // The debug check of a plan: its tables copied to the host, each head's
@@ -1021,7 +1014,6 @@ static void make_columns(mmi_plan* P) {
 static void plan_check(mmi_plan* P) {
   HIPCHK(hipSetDevice(P->ctx->device));
   sync_plan(P);
-  make_columns(P);
   auto get = [](const int32_t* src, size_t n) {
     std::vector<int32_t> v(std::max<size_t>(n, 1));
     if (n) HIPCHK(hipMemcpy(v.data(), src, n * 4, hipMemcpyDeviceToHost));
@@ -1039,7 +1031,9 @@ static void plan_check(mmi_plan* P) {
            hd.gcap);
     const std::vector<int32_t> qp = hd.qperm ? get(hd.qperm, (size_t)hd.nbq * B) : std::vector<int32_t>();
     const std::vector<int32_t> kp = hd.kperm ? get(hd.kperm, (size_t)hd.nbk * B) : std::vector<int32_t>();
-    const std::vector<int32_t> rp = get(hd.rowptr, hd.nbq + 1), col = get(P->col[h], H.nnz);
+    const std::vector<int32_t> rp = get(hd.rowptr, hd.nbq + 1);
+    std::vector<int32_t> col((size_t)H.nnz);
+    column_list(P, h, col.data());
     uptr[h] = get(hd.growptr, (size_t)gp[1] + 1);
     const std::vector<int32_t> ent = get(hd.gcol, H.gnnz);
     if (rp[hd.nbq] != H.nnz || uptr[h][gp[1]] != H.gnnz)
@@ -1437,7 +1431,7 @@ int mmi_plan_export(mmi_plan* P, int head, int what, int slot, void* dst, size_t
         break;
       }
       case MMI_EXPORT_ROW_PTR: src = hd.rowptr; n = (size_t)(hd.nbq + 1) * 4; break;
-      case MMI_EXPORT_COL_IDX: make_columns(P); src = P->col[head]; n = (size_t)H.nnz * 4; break;
+      case MMI_EXPORT_COL_IDX: n = (size_t)H.nnz * 4; break;
       case MMI_EXPORT_V_SCORES: src = e->v; n = e->v ? (size_t)e->L_c * 4 : 0; break;
       case MMI_EXPORT_U_SCORES: src = e->u; n = e->u ? (size_t)e->L_c * 4 : 0; break;
       case MMI_EXPORT_FOLD: src = e->fold; n = e->fold ? (size_t)std::max(0, e->hi - e->lo + 1) * FOLD_W * 4 : 0; break;
@@ -1476,7 +1470,8 @@ int mmi_plan_export(mmi_plan* P, int head, int what, int slot, void* dst, size_t
     if (!dst) return;
     if (bytes < n) fail(MMI_ERR_INVALID_ARG, "destination holds %zu bytes, %zu needed", bytes, n);
     if (n == 0) return;
-    if (!tmp.empty()) std::memcpy(dst, tmp.data(), n);
+    if (what == MMI_EXPORT_COL_IDX) column_list(P, head, static_cast<int32_t*>(dst));
+    else if (!tmp.empty()) std::memcpy(dst, tmp.data(), n);
     else HIPCHK(hipMemcpy(dst, src, n, hipMemcpyDeviceToHost));
   });
 }

@@ -63,3 +63,26 @@ def test_block_statistics(ctx):
                 p = plan.export(h, "params", m)
                 assert (st.sigma[m], st.phase[m]) == (p[0], p[1]), (h, m)
     plan.destroy()
+
+
+def test_column_list_takes_no_device_memory(ctx):
+    """Asking for the size of a column list, or for the list, leaves the plan's device memory as it was."""
+    import ctypes as ct
+    from paper_2504_16083_amd import mmi
+    print("[gpu] column list", flush=True)
+    S = 4097
+    g = torch.Generator().manual_seed(2)
+    q, k = (torch.randn(S, h, 128, generator=g).to(torch.bfloat16).cuda() for h in (4, 2))
+    plan = mmi.Plan(ctx, mmi.Problem(S, 4, 2, None), [C.global_head(C.vslash(50, 50))] * 4, q, k)
+    before = plan.timing()["device_bytes"]
+    need = ct.c_size_t()
+    assert mmi.lib().mmi_plan_export(plan.h, 1, 3, 0, None, 0, ct.byref(need)) == 0
+    assert need.value == 4 * plan.stats(1).nnz_blocks
+    assert plan.timing()["device_bytes"] == before
+    small = np.full(3, -7, np.int32)       # too small: refused, nothing written
+    assert mmi.lib().mmi_plan_export(plan.h, 1, 3, 0, small.ctypes.data_as(ct.c_void_p), 12, ct.byref(need)) == -1
+    assert (small == -7).all()
+    ptr, col = plan.export(1, "row_ptr"), plan.export(1, "col_idx")
+    assert len(col) == ptr[-1] and all((np.diff(col[a:b]) > 0).all() for a, b in zip(ptr, ptr[1:]))
+    assert plan.timing()["device_bytes"] == before
+    plan.destroy()
