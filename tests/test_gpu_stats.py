@@ -34,6 +34,40 @@ def test_sqerr(S, H, n_class):
     assert np.abs(out.cpu().numpy().reshape(H, -1) - want).max() <= S * 128 * 2.0 ** -53 * max(want.max(), 1.0)
 
 
+# the search sums 64 runs of rows per head: empty runs, one row a run, runs of 2 with a short last one, more rows a run
+# than a workgroup reads at once, and past an unrolled stretch
+@pytest.mark.parametrize("S", [5, 64, 127, 2049, 8300])
+def test_search_errors(ctx, S):
+    """The candidates' errors that the search reports, against fp64 sums over the outputs of the same plans."""
+    from paper_2504_16083_amd import mmi
+    print(f"[gpu] search errors S={S}", flush=True)
+    g = torch.Generator().manual_seed(S)
+    q, k, v = (torch.randn(S, h, 128, generator=g).to(torch.bfloat16).cuda() for h in (2, 1, 1))
+    mod = (np.arange(S) * 5 // S % 2).astype(np.uint8)       # five stretches, two modalities
+    prob = mmi.Problem(S, 2, 1, mod)
+    cands = [C.ashape(2, 3), C.ashape(40, 200)]
+    _, r = mmi.mmi_search(ctx, prob, q, k, v, cands, [C.none()], C.ashape(16, 64))
+
+    def out(head):
+        o = torch.empty_like(q)
+        mmi.mmi_attention(ctx, prob, [head] * 2, q, k, v, o)
+        return o.float().cpu()
+
+    def check(got, d, rows):
+        want = d[rows].sum()
+        # fp64 sums of n positive terms in another order: n 2^-53 relative
+        assert abs(got - want) <= S * 128 * 2.0 ** -53 * want, (got, want)
+
+    inner, full = out(C.boundary2d_head({0: C.dense(), 1: C.dense()}, {})), out(C.global_head(C.dense()))
+    for c, op in enumerate(cands):
+        d1 = (out(C.boundary2d_head({0: op, 1: op}, {})) - inner).double().square().sum(2).numpy()
+        d3 = (out(C.global_head(op)) - full).double().square().sum(2).numpy()
+        for h in range(2):
+            for i in range(2):
+                check(r["step1_err"][h, c, i], d1[:, h], mod == i)
+            check(r["step3g_err"][h, c], d3[:, h], slice(None))
+
+
 def test_block_statistics(ctx):
     from paper_2504_16083_amd import mmi
     S = 2049 + 64 * 70                      # more than one run of query blocks per workgroup, a ragged tail
