@@ -238,6 +238,9 @@ int mmi_plan_create(mmi_ctx* ctx, const mmi_problem* prob, const mmi_head_cfg* c
 int mmi_plan_execute(mmi_plan* plan, const void* q, const void* k, const void* v,
                      void* o, float* lse, void* stream);
 
+/* The first call on a plan counts every head on the device (synchronises with
+ * the plan's stream; a device buffer of about S bytes for the time of the
+ * call), later ones read those counts. */
 int mmi_plan_stats(mmi_plan* plan, int head, mmi_head_stats* out);
 
 /* Copy one plan array of `head` to host memory. slot selects the op:

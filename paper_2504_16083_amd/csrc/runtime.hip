@@ -1385,8 +1385,8 @@ int mmi_plan_timing_get(mmi_plan* P, mmi_plan_timing* out) {
     HIPCHK(hipEventElapsedTime(&t.index_ms, P->ev[2], P->ev[3]));
     if (P->executed) {
       HIPCHK(hipEventElapsedTime(&t.attn_ms, P->ev[4], P->ev[5]));
-      // the replays of a captured execute record the stage events
-      if (!P->captured || hipEventElapsedTime(&t.combine_ms, P->ev[5], P->ev[6]) != hipSuccess) {
+      // the replays of a captured execute record the stage events (ev[6] is then not older than ev[5])
+      if (!P->captured || hipEventElapsedTime(&t.combine_ms, P->ev[5], P->ev[6]) != hipSuccess || t.combine_ms < 0) {
         (void)hipGetLastError();
         HIPCHK(hipEventElapsedTime(&t.combine_ms, P->ev[5], P->ev_end ? P->ev_end : P->ev[6]));
       }
