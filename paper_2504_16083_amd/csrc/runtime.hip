@@ -171,8 +171,11 @@ struct Lane {
   uint64_t used = 0;               // execute that used it last
 };
 constexpr size_t NLANES = 8;       // launches of one plan that may overlap
-// Events that other streams of the same device wait for.
-constexpr unsigned ORDER_EVENT = hipEventReleaseToDevice;
+// Events take stage times and order streams of one device, for which the end
+// of each kernel has made its writes visible: a system fence would cost 1.3 us
+// an event. The host therefore never waits for an event: it makes a stream
+// wait for it and synchronises with the stream, which has the fence.
+constexpr unsigned EVENT_FLAGS = hipEventDisableSystemFence;
 
 struct mmi_plan {
   mmi_ctx* ctx = nullptr;
@@ -802,8 +805,7 @@ static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi
   // estimation -> choices
   const Tensor tq{q, p.q_stride_s, p.q_stride_h}, tk{k, p.k_stride_s, p.k_stride_h};
   if (!P->scratch)
-    for (int i = 0; i < 7; ++i)      // streams wait for 3; the others are for stage times only
-      HIPCHK(hipEventCreateWithFlags(&P->ev[i], i == 3 && !P->one_shot ? ORDER_EVENT : hipEventDisableSystemFence));
+    for (auto& e : P->ev) HIPCHK(hipEventCreateWithFlags(&e, EVENT_FLAGS));
   // members of the estimation groups that read the same keys: row sets per
   // KV head, score jobs per (KV head, key map)
   auto grouped = [](int n, auto key_of, int& ngrp, int& nr) {
@@ -951,12 +953,11 @@ static void plan_create_impl(mmi_ctx* ctx, const mmi_problem* prob_in, const mmi
   P->gnnz_all = gnnz_all;
 }
 
-// Waits until the plan's creation and what runs on its stream are done (after
-// a captured execute, or one on another stream, that stream alone does not
-// cover the creation).
+// Waits until what the plan's stream does and the plan's creation are done
+// (after a captured execute that stream alone does not cover the creation).
 static void sync_plan(mmi_plan* P) {
+  if (P->ev[3] && !P->one_shot) HIPCHK(hipStreamWaitEvent(P->stream, P->ev[3], 0));
   HIPCHK(hipStreamSynchronize(P->stream));
-  if (P->ev[3] && !P->one_shot) HIPCHK(hipEventSynchronize(P->ev[3]));
 }
 
 // What mmi_plan_stats takes from the device, for every head of the plan (the
@@ -1115,7 +1116,7 @@ static Lane* lane_for(mmi_plan* P, hipStream_t st) {
   if (i == P->lanes.size()) {
     if (i < most) {
       Lane l;
-      if (!P->one_shot) HIPCHK(hipEventCreateWithFlags(&l.done, ORDER_EVENT));
+      if (!P->one_shot) HIPCHK(hipEventCreateWithFlags(&l.done, EVENT_FLAGS));
       P->lanes.push_back(l);
     } else {
       i = 0;
@@ -1311,9 +1312,9 @@ int mmi_plan_destroy(mmi_plan* plan) {
     if (!plan) fail(MMI_ERR_INVALID_ARG, "plan is NULL");
     (void)hipSetDevice(plan->ctx->device);
     // the buffers go to the next plan: every launch that reads them is over
-    sync_plan(plan);
     for (auto& l : plan->lanes)
-      if (l.done) HIPCHK(hipEventSynchronize(l.done));
+      if (l.done) HIPCHK(hipStreamWaitEvent(plan->stream, l.done, 0));
+    sync_plan(plan);
     free_plan_buffers(plan);
     for (auto& e : plan->ev)
       if (e) (void)hipEventDestroy(e);
