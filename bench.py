@@ -41,7 +41,7 @@ FLOP_PER_BLOCK = 4 * 64 * 64 * 128
 # reported as null.
 TRAFFIC_SOURCES = ("k_attention.hip", "k_blocks.hip", "runtime.hip")
 TRAFFIC = {
-    "3251d9978039392b": {"workload": "cfg4_mm_1m", "fetch_kib": 478466871, "write_kib": 8000374,
+    "2d34bbb56d09cafc": {"workload": "cfg4_mm_1m", "fetch_kib": 463430358, "write_kib": 7999865,
                          "fetch_scale": 1.969, "write_scale": 1.000},
 }
 
