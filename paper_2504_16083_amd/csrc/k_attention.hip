@@ -690,6 +690,8 @@ __global__ __launch_bounds__(128 * R) __attribute__((amdgpu_waves_per_eu(R == 4 
   }
   if (!a.queue) return;
   // the last workgroup clears the counters for the next launch of this queue
+  // (no add is in flight: each is followed by a take of its own thread, whose
+  // returned value is waited for)
   if (threadIdx.x == 0 && atomicAdd(&a.queue[16 * QUEUE_LINE], 1) == (int)gridDim.x - 1) {
     for (int q = 0; q <= 16; ++q)
       __hip_atomic_store(&a.queue[q * QUEUE_LINE], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

@@ -162,13 +162,12 @@ struct HostHead {
 
 }  // namespace mmi
 
-// What one execute of a plan uses alone: item counters (set `index in
-// mmi_plan::lanes` of d_queues) and, if the plan has split row groups, the
-// plan's only split partials.
+// What one execute of a plan uses alone: item counters (lane i of a plan has
+// set i of d_queues) and, if the plan has split row groups, its only partials.
 struct Lane {
   hipStream_t stream = nullptr;    // stream of its last launch
   hipEvent_t done = nullptr;       // after that launch (none in a one-shot plan: one stream, one execute)
-  uint64_t used = 0;               // execute that used it last
+  uint64_t used = 0;               // last execute whose end `done` has recorded
 };
 constexpr size_t NLANES = 8;       // launches of one plan that may overlap
 // Events take stage times and order streams of one device, for which the end
@@ -1129,7 +1128,6 @@ static Lane* lane_for(mmi_plan* P, hipStream_t st) {
   // be filling the work list and clearing the counters on its own stream
   if (l->done) HIPCHK(hipStreamWaitEvent(st, l->used ? l->done : P->ev[3], 0));
   l->stream = st;
-  l->used = ++P->executes;
   return l;
 }
 
@@ -1165,8 +1163,12 @@ static void plan_execute_impl(mmi_plan* P, const void* q, const void* k, const v
   mark(P, 5, st);
   if (e == hipSuccess) e = launch_combine(a, P->d_splits, P->nsplit, st);
   P->captured = !lane;
-  if (lane && lane->done) HIPCHK(hipEventRecord(P->ev_end = lane->done, st));   // also behind a launch whose merge failed
-  else mark(P, 6, st);
+  if (lane && lane->done) {              // also behind a launch whose merge failed
+    HIPCHK(hipEventRecord(P->ev_end = lane->done, st));
+    lane->used = ++P->executes;
+  } else {
+    mark(P, 6, st);
+  }
   HIPCHK(e);
   P->executed = true;
 }
